@@ -434,7 +434,7 @@ hipError_t enqueue_chunks(xtm_lattice_s* L, xtm_particles_s* P, const ChunkPlan&
                                L->n_el, soa, in, P->ctrl, P->alive_upper, c.block, k,
                                c.backward ? 1 : 0, kr, s);
     else if (c.line)
-      e = launch_line(*c.line, L->n_el, soa, in, P->ctrl, P->alive_upper, c.block, k,
+      e = launch_line(*c.line, L->n_el, soa, in, P->ctrl, P->alive_upper, k,
                       c.backward ? 1 : 0, kr, s);
     else
       e = launch_track(c.tab, L->n_el, soa, in, P->ctrl, P->alive_upper, c.block, k,
@@ -570,6 +570,7 @@ xtm_status run_turns(xtm_lattice_s* L, xtm_particles_s* P, int32_t n_turns,
       }
     }
     if (lk.ok) {
+      if (P->alive_upper > kWideParticles) build_wide_form(&lk);
       c.variant = want;
       c.line = &lk;
       c.block = line_block(want - 5);

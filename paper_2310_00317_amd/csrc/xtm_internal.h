@@ -177,6 +177,10 @@ struct LineKernel {
   int32_t* cells_d = nullptr;  // per cell: kind, first parameter word, first element, words
   std::string source;
   std::string error;
+  // the wide form of the same kernel, on the same arrays (build_wide_form)
+  std::string wide_source;
+  bool wide_tried = false;
+  hipFunction_t wide_fn = nullptr;
 };
 // Generated-kernel forms ("styles"), all computing the same maps in the same
 // order: the workgroup (256 lanes or one wave), the way element code reads
@@ -236,8 +240,18 @@ bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKer
 hipError_t launch_line_record(const LineKernel& k, int32_t n_el, const double* c6, int64_t n,
                               double* out, bool all_rows, KernelRef r, hipStream_t s);
 void free_line_kernel(LineKernel* k);
+// Largest number of alive particles that the form staging its parameters in
+// LDS serves where a wide form exists: one wave on each of 1,024 SIMDs.
+// Up to there a wave has its SIMD to itself and LDS is the faster source
+// (FODO ring, 65,536 particles: 0.82 ms against 0.91 ms for 20 turns; DA ring
+// 6.45 against 6.56 ms for 3); above, the scalar registers (DA ring, 81,920:
+// 9.7 against 10.8 ms; FODO ring level to 131,072, then 1-4 % better; error
+// seeds 25 % better at 131,072).
+constexpr int32_t kWideParticles = 65536;
+// Compile the wide form (once; nothing if the kernel has none).
+void build_wide_form(LineKernel* k);
 hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,
-                       const int32_t* ctrl, int64_t grid_upper, int32_t block, int32_t n_turns,
+                       const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,
                        int32_t backward, KernelRef r, hipStream_t s);
 hipError_t launch_line_batched(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,
                                const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,

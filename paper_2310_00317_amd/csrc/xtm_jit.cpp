@@ -60,6 +60,14 @@ constexpr int kMaxCode = 48;
 // the long-cell forms
 constexpr int kLongUnit = 40;
 constexpr int kLongCode = 64;
+// parameter words between two settled points of a straight cell, at least:
+// every drift of the FODO and DA rings (12 and 23 words apart), every second
+// or third of a ring of sliced magnets (5 to 8 words a slice).  More between
+// them costs the first two registers (DA ring, 40,000 particles: 4.05e11
+// passes/s settled at every drift, 3.79e11 at every second, 3.38e11 at none),
+// less costs the last overlap (thick ring, 30,000: 3.48e11 at every drift,
+// 3.65e11-3.80e11 at every second to fourth)
+constexpr int32_t kSettleWords = 12;
 // the recording kernel buffers a cell's rows in LDS: at most 16 elements a
 // cell (16 x 64 lanes x 48 bytes)
 constexpr int kMaxRecordUnit = 16;
@@ -143,12 +151,22 @@ int32_t n_words(uint32_t s) {
 // kRecord: the maps for optics by tracking (apertures not applied; a lane
 // whose drift finds no real longitudinal momentum keeps its entry
 // coordinates and applies no further maps).
-enum EmitMode { kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kRecord = 3 };
+// kFlag: no branch and no store; a failing test, or operands the drift's short
+// sequences do not serve, set `bad`.
+// kTest: the generic drift, and a loss test's result in `ok` with the state a
+// lost particle takes in `ls`.
+// kFlagScalar: as kFlag, the parameters in scalar registers.
+enum EmitMode {
+  kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kRecord = 3, kFlag = 4, kTest = 5, kFlagScalar = 6
+};
 
+// curv_lr: every bend with a curvature term has a positive radiation length.
 std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool far_rf,
-                 EmitMode mode) {
+                 EmitMode mode, bool curv_lr = false) {
   const uint32_t kt = s & 0xffu, order = (s >> 8) & 0xffu;
   auto P = [&](int32_t m) { return "(" + arr + ")[" + std::to_string(m) + "]"; };
+  const bool flag = mode == kFlag || mode == kFlagScalar;
+  const std::string sc = mode == kFlagScalar ? ", true" : "";  // multipole's second parameter
   std::ostringstream c;
   switch (kt) {
     case K_DRIFT: {
@@ -156,6 +174,13 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       const std::string any = std::to_string(order);
       if (mode == kReplay)
         c << "(void)xtmm::drift_exact(q, " << P(0) << ", " << any << ");";
+      else if (flag)
+        c << "xtmm::drift_flag<" << (mode == kFlagScalar ? "true" : "false") << ">(q, " << P(0)
+          << ", " << any << ", bad);";
+      else if (mode == kTest)
+        c << "{ const xtmm::DriftIn d_ = xtmm::drift_in(q); double lp_, dq_; "
+          << "xtmm::drift_generic(" << P(0) << ", d_, lp_, dq_); "
+          << "xtmm::drift_apply(q, lp_, dq_); ok = d_.pz2 > 0.0; ls = -1; }";
       else if (mode == kRecord)
         c << "{ const xtmm::Pt q0_ = q; if (!xtmm::drift_exact(q, " << P(0) << ", " << any
           << ")) { q = q0_; alive = false; } }";
@@ -176,24 +201,25 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       c << "xtmm::drift_expanded(q, " << P(0) << ");";
       break;
     case K_MULT:
-      c << "{ double kx, ky; xtmm::multipole<" << order << ">(q, " << arr << ", kx, ky); }";
+      c << "{ double kx, ky; xtmm::multipole<" << order << sc << ">(q, " << arr << ", kx, ky); }";
       break;
     case K_MULT_CURV: {
       const int32_t v = 2 * ((int32_t)order + 1);
-      c << "{ double kx, ky; xtmm::multipole<" << order << ">(q, " << arr
-        << ", kx, ky); xtmm::curvature(q, " << P(v) << ", " << P(v + 1) << ", " << P(v + 2)
+      c << "{ double kx, ky; xtmm::multipole<" << order << sc << ">(q, " << arr
+        << ", kx, ky); xtmm::curvature<" << (curv_lr ? "true" : "false") << ">(q, " << P(v) << ", " << P(v + 1) << ", " << P(v + 2)
         << "); RAD(kx, ky, " << P(v + 2) << ", " << j << "); }";
       break;
     }
     case K_MULT_LR: {
       const int32_t v = 2 * ((int32_t)order + 1);
-      c << "{ double kx, ky; xtmm::multipole<" << order << ">(q, " << arr
+      c << "{ double kx, ky; xtmm::multipole<" << order << sc << ">(q, " << arr
         << ", kx, ky); RAD(kx, ky, " << P(v) << ", " << j << "); }";
       break;
     }
     case K_RF:
       c << (far_rf ? "xtmm::rf_far(q, " : "xtmm::rf(q, ") << P(0) << ", " << P(1) << ", " << P(2)
         << ", beta0, two_over_beta0);";
+      if (flag) c << " bad |= !xtmm::drift_range(q);";
       break;
     case K_SHIFT:
       c << "xtmm::xyshift(q, " << P(0) << ", " << P(1) << ");";
@@ -209,6 +235,14 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       if (kt == K_AP_CIRC) test = "xtmm::in_circle(q, " + P(0) + ")";
       else if (kt == K_AP_ELL) test = "xtmm::in_ellipse(q, " + P(0) + ", " + P(1) + ")";
       else test = "xtmm::in_rect(q, " + P(0) + ", " + P(1) + ", " + P(2) + ", " + P(3) + ")";
+      if (flag) {
+        c << "bad |= !" << test << ";";
+        break;
+      }
+      if (mode == kTest) {
+        c << "ok = " << test << "; ls = 0;";
+        break;
+      }
       c << "{ const bool ok = " << test << "; ";
       if (mode == kSaveAtLoss)
         c << "if (!ok && live) { SAVE(); code = e0 + " << j << "; st = 0; live = false; } }";
@@ -234,7 +268,8 @@ int32_t kind_words(const std::vector<uint32_t>& k) {
 // memory and writes it to the other slot before the cell barrier.  Element
 // code then reads its parameters as broadcast LDS reads at compile-time
 // offsets.
-std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_form) {
+std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_form,
+                     bool scalar, bool curv_lr) {
   int32_t maxw = 1;
   for (const auto& k : d.kinds) maxw = std::max(maxw, kind_words(k));
   // the lanes of a workgroup share one LDS slot pair, filled by all of them
@@ -250,11 +285,38 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   // per cell (line_deferred: the tests only record the loss code; lanes lost
   // in the cell replay it afterwards)
   const bool deferred = line_deferred(style);
+  // (line_long) or once per cell without recording which test failed: the
+  // cell is one straight run of arithmetic, and lanes that failed some test
+  // in it, or met a drift outside the short sequences' window, go through it
+  // again from its entry with each test where it belongs.
+  //   What bounds it: a wave alone on its SIMD waits on its own dependent
+  //   operations (a drift is 17 of them from momenta to positions), and a
+  //   branch per drift and per aperture kept the next element's operations,
+  //   and the drift's quotient for zeta that nothing waits for, from filling
+  //   those waits.  Without the branches (and with 38 instead of 40 operations
+  //   a drift, see drift_flag): FODO ring, 1,000 particles, 47 -> 38 us per
+  //   turn; DA ring, 40,000 particles, 3.5e11 -> 4.05e11 passes/s; sliced
+  //   ring, 30,000 particles, 3.1e11 -> 3.6e11.
+  //   The register constraints below hold the compiler to one drift's work in
+  //   flight: left alone it keeps every pending quotient and parameter of the
+  //   cell in registers (over 300, one wave per SIMD, 1M particles of the
+  //   FODO ring 12.1 ms instead of 8.4 ms).
+  // The wide form (`scalar`): the parameters come through scalar loads into
+  // scalar registers, which a fused multiply-add takes as its addend.  With
+  // several waves per SIMD the broadcast reads of LDS bound the rings of high
+  // order multipoles (an order-10 multipole reads 11 x 16 bytes for 64 lanes
+  // and computes 42 operations) and their registers kept the waves at two per
+  // SIMD; in scalar registers they cost neither (118-160 vector registers,
+  // three or four waves).  Error seeds of the FODO ring, 1M particles: 6.1e11
+  // -> 8.8e11 passes/s; DA ring, 131,072: 6.3e11 -> 7.8e11; FODO ring, 1M:
+  // 1.95e12 -> 2.0e12.  A lone wave waits longer for scalar loads (one every
+  // 64 bytes) than for LDS: DA ring, 40,000 particles, 3.8e11 against 4.05e11.
+  const bool flagged = line_long(style) && rad_form == 0;
   // particles per lane (line_ppt): one, or two whose maps interleave
   const int32_t ppt = line_ppt(style);
   std::vector<uint32_t> sigs;  // distinct element signatures of the line
   std::string replay_tables;   // per kind: first entry; per entry: signature, offset
-  if (deferred) {
+  if (deferred || flagged) {
     std::ostringstream kf, es, eo;
     int32_t n = 0;
     for (const auto& k : d.kinds) {
@@ -310,21 +372,27 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
        "    P.x[pj_] = q.x; P.px[pj_] = q.px; P.y[pj_] = q.y; P.py[pj_] = q.py; \\\n"
        "    P.zeta[pj_] = q.zeta; P.delta[pj_] = q.delta; P.ptau[pj_] = q.ptau; \\\n"
        "    P.rpp[pj_] = q.rpp; P.rvv[pj_] = q.rvv; } while (0)\n"
+       "typedef const __attribute__((address_space(3))) double* lds_double;\n"
+       "typedef const __attribute__((address_space(4))) double* cst_double;\n"
        "#define MAXW " << maxw << "\n"
        "#define PER_THREAD " << per_thread << "\n"
        "#define LANES " << lanes << "\n"
        "#define PPT " << ppt << "\n"
        << replay_tables <<
-       "extern \"C\" __global__ void __launch_bounds__(" << lanes << ")\n"
+       "extern \"C\" __global__ void __launch_bounds__(" << lanes << ")"
+    << (scalar ? " __attribute__((amdgpu_waves_per_eu(3, 4)))\n" : "\n") <<
        "xtm_line(const double* __restrict__ " << (batched ? "prm_all" : "prm")
     << ", const int* __restrict__ cells, int n_cells,\n"
        "         int n_el, SoA P, const int* __restrict__ idx, const int* __restrict__ ctrl,\n"
-       "         int n_turns, int backward, KRef r"
+       "         int n_turns, int backward, int n_min, int n_max, KRef r"
     << (batched ? ",\n         const int* __restrict__ first_slot, int nv, long long prm_stride"
                 : "")
     << ") {\n";
-  s << "  __shared__ double slot[2 * MAXW];\n"
-       "  const int lane = threadIdx.x;\n";
+  if (!scalar) s << "  __shared__ double slot[2 * MAXW];\n";
+  s << "  const int lane = threadIdx.x;\n"
+       "  (void)lane;\n"
+       "  // another form serves this number of particles\n"
+       "  if (ctrl[0] <= n_min || ctrl[0] > n_max) return;\n";
   // a batch of lattice variants with one cell structure: each slot belongs
   // to the variant whose slot range holds it; the wave makes one pass per
   // variant among its lanes (smallest first), reading that variant's
@@ -426,17 +494,18 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "    xtmm::refresh(q, beta0);\n"
          "  }\n";
   }
-  s <<        "  {\n"
-       "    const int off0 = cells[1], nw0 = cells[3];\n"
-       "    for (int w = lane; w < nw0; w += LANES) slot[w] = prm[off0 + w];\n"
-       "  }\n";
-  s << "  __syncthreads();\n";
+  if (!scalar)
+    s << "  {\n"
+         "    const int off0 = cells[1], nw0 = cells[3];\n"
+         "    for (int w = lane; w < nw0; w += LANES) slot[w] = prm[off0 + w];\n"
+         "  }\n"
+         "  __syncthreads();\n"
+         "  int b = 0;\n";
   // the cell table read one record (kind, first word, first element, words)
   // at a time, one cell ahead: the current cell's record came with the
   // previous cell's, so a cell starts with one scalar load, not three in
   // sequence
-  s << "  int b = 0;\n"
-       "  const int4* __restrict__ cells4 = reinterpret_cast<const int4*>(cells);\n"
+  s << "  const int4* __restrict__ cells4 = reinterpret_cast<const int4*>(cells);\n"
        "  int4 rc = cells4[0];\n"
        "  for (int t = 0; t < n_turns; ++t) {\n"
        "    const int enc_t = t * n_el + 1;\n";
@@ -460,25 +529,29 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
        "    for (int c = 0; c < n_cells; ++c) {\n"
        "      const int cn = (c + 1 == n_cells) ? 0 : c + 1;\n"
        "      const int4 rn = cells4[cn];\n"
-       "      const int offn = rn.y, nwn = rn.w;\n"
-       "      // every lane loads (past the cell's words, its first word; the\n"
-       "      // parameter array ends in a pad word): no branch around the loads\n"
-       "      double pre[PER_THREAD];\n"
-       "#pragma unroll\n"
-       "      for (int k = 0; k < PER_THREAD; ++k) {\n"
-       "        const int w = lane + k * LANES;\n"
-       "        const double v_ = prm[offn + (w < nwn ? w : 0)];\n"
-       "        pre[k] = (w < nwn) ? v_ : 0.0;\n"
-       "      }\n"
        "      const int kind = rc.x;\n"
-       "      const int ec = rc.z;\n"
-       "      // slot base hidden behind a register move: element reads become\n"
-       "      // base + immediate-offset LDS loads instead of hoisted constant selects\n"
-       "      int base;\n"
-       "      asm volatile(\"v_mov_b32 %0, %1\" : \"=v\"(base) : \"s\"(b * MAXW));\n"
-       "      // (the mask tells the compiler the base is small and non-negative, which\n"
-       "      // lets it fold the element offsets into the LDS instructions)\n"
-       "      const double* p = &slot[base & 0x3fff];\n"
+       "      const int ec = rc.z;\n";
+  if (!scalar)
+    s << "      const int offn = rn.y, nwn = rn.w;\n"
+         "      // every lane loads (past the cell's words, its first word; the\n"
+         "      // parameter array ends in a pad word): no branch around the loads\n"
+         "      double pre[PER_THREAD];\n"
+         "#pragma unroll\n"
+         "      for (int k = 0; k < PER_THREAD; ++k) {\n"
+         "        const int w = lane + k * LANES;\n"
+         "        const double v_ = prm[offn + (w < nwn ? w : 0)];\n"
+         "        pre[k] = (w < nwn) ? v_ : 0.0;\n"
+         "      }\n"
+         "      // the slot as an LDS pointer passed through an empty register\n"
+         "      // constraint: element reads become base + immediate-offset LDS loads\n"
+         "      // instead of hoisted constant selects\n"
+         "      lds_double p = (lds_double)slot + b * MAXW;\n"
+         "      asm volatile(\"\" : \"+v\"(p));\n";
+  else
+    s << "      // the cell's words, read with scalar loads\n"
+         "      cst_double p = (cst_double)(unsigned long long)(prm + rc.y);\n"
+         "      asm volatile(\"\" : \"+s\"(p));\n";
+  s <<
        "      // the cell's loss-code base lives in a VGPR so the per-element codes\n"
        "      // e0 + j are vector adds of literals, not hoisted scalar constants\n"
        "      int e0;\n"
@@ -486,6 +559,9 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   if (deferred)
     s << "      const int code_in = code;\n"
          "      const xtmm::Pt qc = q;\n";
+  if (flagged)
+    s << "      const xtmm::Pt qc = q;\n"
+         "      bool bad = !xtmm::drift_range(q);\n";
   for (size_t k = 0; k < d.kinds.size(); ++k) {
     s << "      " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
     const auto& kd = d.kinds[k];
@@ -514,19 +590,34 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
       read_before[m] = (short_prev && m >= 2 && n_words(kd[m]) >= 8) ? m - 2 : m - 1;
     }
     if (fetch == 2 && !kd.empty()) load(0);
+    int32_t since = 0;  // parameter words since the last settled point
     for (size_t j = 0; j < kd.size(); ++j) {
       std::string arr = "p + " + std::to_string(off[j]);
       if (fetch == 1) {
         load(j);
         s << "        __builtin_amdgcn_sched_barrier(0);\n";
       } else if (fetch == 2) {
+        if (flagged) {
+          // a drift starts from settled momenta, and the reads that follow
+          // stay behind this point (both pass through an empty register
+          // constraint); in between, the arithmetic may move
+          const uint32_t kt = kd[j] & 0xffu;
+          const bool settle = (kt == K_DRIFT || kt == K_DRIFT_EXP) && since >= kSettleWords;
+          if (settle) since = 0;
+          since += n_words(kd[j]);
+          s << "        asm volatile(\"\" : \"+" << (scalar ? "s" : "v") << "\"(p)"
+            << (settle ? ", \"+v\"(q.px), \"+v\"(q.py), \"+v\"(q.zeta)" : "") << ");\n";
+        }
         for (size_t m = j + 1; m < kd.size() && m <= j + 2; ++m)
           if (read_before[m] == j) load(m);
-        s << "        __builtin_amdgcn_sched_barrier(0);\n";
+        if (!flagged) s << "        __builtin_amdgcn_sched_barrier(0);\n";
       }
       if (fetch != 0 && n_words(kd[j]) > 0) arr = "w" + std::to_string(j);
       const std::string stmt =
-          emit(kd[j], arr, std::to_string(j), far_rf, deferred ? kMarkOnly : kSaveAtLoss);
+          emit(kd[j], arr, std::to_string(j), far_rf,
+               scalar ? kFlagScalar
+                      : (flagged ? kFlag : (deferred ? kMarkOnly : kSaveAtLoss)),
+               curv_lr);
       if (stmt.empty()) continue;
       if (ppt == 1) {
         s << "        " << stmt << "\n";
@@ -567,14 +658,44 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "        }\n"
          "      }\n";
   }
+  if (flagged) {
+    // the rare second pass through the cell: from the entry copy, element by
+    // element, with the generic drift and the loss test where they belong
+    s << "      bad |= !(q.x == q.x);\n"
+         "      bad &= live;\n"
+         "      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {\n"
+         "        if (bad) {\n"
+         "          q = qc;\n"
+         "          for (int j = kind_first[kind]; j < kind_first[kind + 1]; ++j) {\n"
+      << (scalar ? "            const double* pe = prm + rc.y + elem_off[j];\n"
+                 : "            const double* pe = (const double*)(p + elem_off[j]);\n")
+      << "            const xtmm::Pt q0 = q;\n"
+         "            bool ok = true;\n"
+         "            int ls = 0;\n"
+         "            switch (elem_sig[j]) {\n";
+    for (size_t g = 0; g < sigs.size(); ++g) {
+      const std::string stmt = emit(sigs[g], "pe", "(j - kind_first[kind])", far_rf, kTest);
+      if (!stmt.empty()) s << "              case " << g << ": " << stmt << " break;\n";
+    }
+    s << "              default: break;\n"
+         "            }\n"
+         "            if (!ok && live) {\n"
+         "              const xtmm::Pt q = q0;\n"
+         "              SAVE(); code = e0 + (j - kind_first[kind]); st = ls; live = false;\n"
+         "            }\n"
+         "          }\n"
+         "        }\n"
+         "      }\n";
+  }
+  if (!scalar)
   s << "#pragma unroll\n"
        "      for (int k = 0; k < PER_THREAD; ++k) {\n"
        "        const int w = lane + k * LANES;\n"
        "        if (w < nwn) slot[(b ^ 1) * MAXW + w] = pre[k];\n"
        "      }\n"
-       "      b ^= 1;\n"
-       "      rc = rn;\n";
-  s << "      __syncthreads();\n";
+       "      b ^= 1;\n";
+  s << "      rc = rn;\n";
+  if (!scalar) s << "      __syncthreads();\n";
   s << "    }\n";
   if (ppt == 1)
     s << "    if (__syncthreads_and(code != 0)) break;\n";
@@ -874,23 +995,25 @@ bool build_line_kernel(const std::vector<uint64_t>& tab, int32_t n_el, int32_t s
 }
 
 namespace {
+// Compile a generated kernel, or take it from the cache; null on failure.
+hipFunction_t cached_function(const std::string& source, const char* name, bool ilp_sched,
+                              std::string* error) {
+  std::lock_guard<std::mutex> lock(g_mu);
+  const std::string key = (ilp_sched ? "ilp\n" : "default\n") + source;
+  auto it = g_cache.find(key);
+  if (it == g_cache.end()) it = g_cache.emplace(key, compile(source, name, ilp_sched)).first;
+  if (!it->second.fn) *error = it->second.error;
+  return it->second.fn;
+}
+
 // Compile (or take from the cache) a generated kernel and upload its
 // parameter array and cell table.
 bool finish_kernel(const Decomp& d, const std::string& source, const char* name,
                    bool ilp_sched, const std::vector<int32_t>& word_of,
                    const std::vector<double>& prm, LineKernel* k) {
   k->source = source;
-  {
-    std::lock_guard<std::mutex> lock(g_mu);
-    const std::string key = (ilp_sched ? "ilp\n" : "default\n") + k->source;
-    auto it = g_cache.find(key);
-    if (it == g_cache.end()) it = g_cache.emplace(key, compile(k->source, name, ilp_sched)).first;
-    if (!it->second.fn) {
-      k->error = it->second.error;
-      return false;
-    }
-    k->fn = it->second.fn;
-  }
+  k->fn = cached_function(source, name, ilp_sched, &k->error);
+  if (!k->fn) return false;
   std::vector<int32_t> cells;  // per cell: kind, first parameter word, first element, words
   for (size_t c = 0; c < d.cell_kind.size(); ++c) {
     cells.push_back(d.cell_kind[c]);
@@ -955,10 +1078,28 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   // single-lattice kernels take the ILP schedule (measured 2-4 % faster on
   // the DA ring and with the mean and Gaussian radiation, 1 % slower on a
   // saturated FODO ring); the batched ones (0.7 % slower with it on 64
-  // variants) and the photon form (4 % slower) keep the default
-  const bool ilp = !batched && rad_form != 2;
-  return finish_kernel(d, generate(d, style, batched, rad_form), "xtm_line", ilp, word_of, prm,
-                       k);
+  // variants) and the photon form (4 % slower) keep the default; the straight
+  // cells take it (with the default, 200 registers instead of 141 on the FODO
+  // ring and 9.4 ms instead of 8.8 ms for 1M particles)
+  const bool flagged = line_long(style) && rad_form == 0;
+  const bool ilp = flagged || (!batched && rad_form != 2);
+  // whether every curvature term has a positive radiation length (a test the
+  // straight cells then leave out)
+  bool curv_lr = flagged;
+  for (int32_t e = 0; e < n_el && curv_lr; ++e)
+    if ((sig[e] & 0xffu) == K_MULT_CURV)
+      for (size_t v = 0; v < tabs.size(); ++v)
+        curv_lr &= prm[v * stride + word_of[e] + n_words(sig[e]) - 1] > 0.0;
+  if (flagged) k->wide_source = generate(d, style, batched, rad_form, true, curv_lr);
+  return finish_kernel(d, generate(d, style, batched, rad_form, false, curv_lr), "xtm_line", ilp,
+                       word_of, prm, k);
+}
+
+void build_wide_form(LineKernel* k) {
+  if (!k->ok || k->wide_tried || k->wide_source.empty()) return;
+  k->wide_tried = true;
+  std::string error;
+  k->wide_fn = cached_function(k->wide_source, "xtm_line", true, &error);
 }
 
 bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKernel* k) {
@@ -985,22 +1126,42 @@ void free_line_kernel(LineKernel* k) {
   k->ok = false;
 }
 
+// The launches of one chunk.  A set that may hold more particles than one wave
+// per SIMD (kWideParticles) is launched on the wide form, which reads its
+// parameters with scalar loads, and on the form that stages them in LDS: the
+// alive count is on the device, and each launch ends at once unless the count
+// is its own.  `args` holds the kernel arguments, the bounds at `n_min` and
+// `n_max`.
+namespace {
+hipError_t launch_forms(const LineKernel& k, int64_t grid_upper, void** args, int32_t* n_min,
+                        int32_t* n_max, hipStream_t s) {
+  const int32_t wg = line_block(k.style);
+  const int64_t per_wg = (int64_t)wg * line_ppt(k.style);  // particles per workgroup
+  const bool wide = k.wide_fn && grid_upper > kWideParticles;
+  *n_min = -1;
+  *n_max = wide ? kWideParticles : INT32_MAX;
+  const int64_t upper = wide ? kWideParticles : grid_upper;
+  hipError_t e = hipModuleLaunchKernel(k.fn, (unsigned)((upper + per_wg - 1) / per_wg), 1, 1,
+                                       (unsigned)wg, 1, 1, 0, s, args, nullptr);
+  if (e != hipSuccess || !wide) return e;
+  *n_min = kWideParticles;
+  *n_max = INT32_MAX;
+  return hipModuleLaunchKernel(k.wide_fn, (unsigned)((grid_upper + per_wg - 1) / per_wg), 1, 1,
+                               (unsigned)wg, 1, 1, 0, s, args, nullptr);
+}
+}  // namespace
+
 hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,
-                       const int32_t* ctrl, int64_t grid_upper, int32_t block, int32_t n_turns,
+                       const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,
                        int32_t backward, KernelRef r, hipStream_t s) {
   if (grid_upper <= 0 || n_turns <= 0) return hipSuccess;
   const double* prm = k.prm_d;
   const int32_t* cells = k.cells_d;
-  int32_t n_cells = k.n_cells;
+  int32_t n_cells = k.n_cells, n_min = 0, n_max = 0;
   void* args[] = {(void*)&prm, (void*)&cells, (void*)&n_cells, (void*)&n_el, (void*)&P,
-                  (void*)&idx, (void*)&ctrl, (void*)&n_turns, (void*)&backward, (void*)&r};
-  // the generated kernel stages each cell's parameters with the stride of
-  // its style's fixed workgroup size (line_block)
-  (void)block;
-  const int32_t wg = line_block(k.style);
-  const int64_t per_wg = (int64_t)wg * line_ppt(k.style);  // particles per workgroup
-  const unsigned grid = (unsigned)((grid_upper + per_wg - 1) / per_wg);
-  return hipModuleLaunchKernel(k.fn, grid, 1, 1, (unsigned)wg, 1, 1, 0, s, args, nullptr);
+                  (void*)&idx, (void*)&ctrl, (void*)&n_turns, (void*)&backward, (void*)&n_min,
+                  (void*)&n_max, (void*)&r};
+  return launch_forms(k, grid_upper, args, &n_min, &n_max, s);
 }
 
 hipError_t launch_line_record(const LineKernel& k, int32_t n_el, const double* c6, int64_t n,
@@ -1025,15 +1186,13 @@ hipError_t launch_line_batched(const LineKernel& k, int32_t n_el, SoA P, const i
   if (!k.batched) return hipErrorInvalidValue;
   const double* prm = k.prm_d;
   const int32_t* cells = k.cells_d;
-  int32_t n_cells = k.n_cells, nv = k.nv;
+  int32_t n_cells = k.n_cells, nv = k.nv, n_min = 0, n_max = 0;
   long long stride = (long long)k.stride;
   void* args[] = {(void*)&prm,  (void*)&cells, (void*)&n_cells, (void*)&n_el,
                   (void*)&P,    (void*)&idx,   (void*)&ctrl,    (void*)&n_turns,
-                  (void*)&backward, (void*)&r, (void*)&first_slot, (void*)&nv, (void*)&stride};
-  const int32_t wg = line_block(k.style);
-  const int64_t per_wg = (int64_t)wg * line_ppt(k.style);  // particles per workgroup
-  const unsigned grid = (unsigned)((grid_upper + per_wg - 1) / per_wg);
-  return hipModuleLaunchKernel(k.fn, grid, 1, 1, (unsigned)wg, 1, 1, 0, s, args, nullptr);
+                  (void*)&backward, (void*)&n_min, (void*)&n_max, (void*)&r,
+                  (void*)&first_slot, (void*)&nv, (void*)&stride};
+  return launch_forms(k, grid_upper, args, &n_min, &n_max, s);
 }
 
 }  // namespace xtm

@@ -26,6 +26,25 @@ __device__ __forceinline__ void refresh(Pt& q, double beta0) {
   q.bpt = beta0 * q.ptau;
 }
 
+// a b + c and c - a b.  kScalar: c is wave-uniform and sits in scalar
+// registers, where the three-operand instruction can read it; written out
+// because the compiler prefers the accumulating form, which needs c in vector
+// registers first (one move per multipole coefficient).
+template <bool kScalar>
+__device__ __forceinline__ double fma_c(double a, double b, double c) {
+  if (!kScalar) return fma(a, b, c);
+  double d;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+template <bool kScalar>
+__device__ __forceinline__ double fnma_c(double a, double b, double c) {
+  if (!kScalar) return fma(-a, b, c);
+  double d;
+  asm("v_fma_f64 %0, -%1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+  return d;
+}
+
 // Square root and quotient for operands well inside the exponent range,
 // both correctly rounded (the same values as sqrt() and a/b, whose generic
 // sequences add exponent-scaling and special-case steps for operands near
@@ -70,12 +89,13 @@ __device__ __forceinline__ double sqrt_in(double x) {
   return sqrt_in(x, h);
 }
 
+template <bool kScalar = false>
 __device__ __forceinline__ double div_by_root(double a, double root, double h) {
   double r = 2.0 * h;
   const double e = fma(-root, r, 1.0);
   r = fma(r, e, r);
   const double q = a * r;
-  const double rho = fma(-root, q, a);
+  const double rho = fnma_c<kScalar>(root, q, a);
   return fma(rho, r, q);
 }
 
@@ -168,6 +188,38 @@ __device__ __forceinline__ bool drift_exact(Pt& q, double L, int len_class = 0) 
   return d.pz2 > 0.0;
 }
 
+// The drift without branches, for a cell whose tests are collected: `bad` is
+// set where the short sequences do not serve the operands.  The caller holds
+// drift_range for the particle's momentum, so of the window only the tests
+// that depend on the transverse momenta are left: with (1+d)^2 in
+// (2^-100, 4), pz^2 = (1+d)^2 - px^2 - py^2 is below 4 and, each rounded
+// difference being zero or at least 2^-53 times its operand, it is above
+// 2^-260 or not positive; then the root is not a number, and so are x and y
+// from there on, which the caller tests once.
+__device__ __forceinline__ bool drift_range(const Pt& q) {
+  return (q.opd2 > 0x1p-100) & (q.opd2 < 4.0);
+}
+
+template <bool kScalar>
+__device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, bool& bad) {
+  const DriftIn d = drift_in(q);
+  double lp, dq;
+  if (len_class == 2) {
+    drift_generic(L, d, lp, dq);
+    bad |= !(d.pz2 > 0.0);
+  } else {
+    double h;
+    const double pz = sqrt_in(d.pz2, h);
+    const double b1 = 1.0 + pz;
+    lp = div_by_root<kScalar>(L, pz, h);
+    dq = div_in(d.a, b1);
+    bad |= !(fabs(d.a) >= 0x1p-600);
+    bad |= b1 == 0x1.fffffffffffffp+0;
+    if (len_class == 1) bad |= all_ones_significand(pz);
+  }
+  drift_apply(q, lp, dq);
+}
+
 // The exact drift's loss test alone.
 __device__ __forceinline__ bool drift_ok(const Pt& q) { return drift_in(q).pz2 > 0.0; }
 
@@ -186,15 +238,15 @@ __device__ __forceinline__ void drift_expanded(Pt& q, double L) {
 // c = (cr_N, ci_N, cr_{N-1}, ci_{N-1}, ..., cr_0, ci_0), by Horner:
 // b <- b z + c_n, re = fma(br, x, fma(-bi, y, cr)), im = fma(br, y, fma(bi, x, ci)).
 // Writes the field kick (dpx, dpy) to kx, ky.
-template <int N>
+template <int N, bool kScalar = false>
 __device__ __forceinline__ void multipole(Pt& q, const double* __restrict__ c, double& kx,
                                           double& ky) {
   double br = c[0], bi = c[1];
 #pragma unroll
   for (int k = 1; k <= N; ++k) {
     const double cr = c[2 * k], ci = c[2 * k + 1];
-    const double tr = fma(br, q.x, fma(-bi, q.y, cr));
-    const double ti = fma(br, q.y, fma(bi, q.x, ci));
+    const double tr = fma(br, q.x, fnma_c<kScalar>(bi, q.y, cr));
+    const double ti = fma(br, q.y, fma_c<kScalar>(bi, q.x, ci));
     br = tr;
     bi = ti;
   }
@@ -206,9 +258,11 @@ __device__ __forceinline__ void multipole(Pt& q, const double* __restrict__ c, d
 
 // Frame curvature of a thin bend: dpx += hxl (1+d) - (knl0 hxl) x / Lr (Lr > 0),
 // zeta -= hxl x (1 + beta0 ptau) rpp.
+// kLr: Lr is known to be positive.
+template <bool kLr = false>
 __device__ __forceinline__ void curvature(Pt& q, double hxl, double k0h, double lr) {
   double dpx = hxl * (1.0 + q.delta);
-  if (lr > 0.0) dpx = dpx - k0h * q.x / lr;
+  if (kLr || lr > 0.0) dpx = dpx - k0h * q.x / lr;
   const double dz = hxl * q.x * (1.0 + q.bpt) * q.rpp;
   q.px = q.px + dpx;
   q.zeta = q.zeta - dz;
