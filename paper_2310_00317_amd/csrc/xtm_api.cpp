@@ -1406,15 +1406,12 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
     hipStream_t s = (hipStream_t)stream;
     const int64_t bmax = batch < n ? batch : n;
     const int64_t wf = mlp_workspace_floats(bmax);
-    float *work = nullptr, *xb = nullptr, *yb = nullptr, *grad = nullptr, *loss = nullptr;
+    float *work = nullptr, *loss = nullptr;
     int32_t* perm_d = nullptr;
     auto release = [&]() {
-      hipFree(work); hipFree(xb); hipFree(yb); hipFree(grad); hipFree(loss); hipFree(perm_d);
+      hipFree(work); hipFree(loss); hipFree(perm_d);
     };
     if (hipMalloc(&work, wf * sizeof(float)) != hipSuccess ||
-        hipMalloc(&xb, bmax * 16 * sizeof(float)) != hipSuccess ||
-        hipMalloc(&yb, bmax * sizeof(float)) != hipSuccess ||
-        hipMalloc(&grad, XTM_MLP_PARAMS * sizeof(float)) != hipSuccess ||
         hipMalloc(&loss, 4096 * sizeof(float)) != hipSuccess ||
         hipMalloc(&perm_d, n * sizeof(int32_t)) != hipSuccess) {
       release();
@@ -1434,11 +1431,8 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
       e = hipMemcpyAsync(perm_d, perm.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s);
       for (int64_t b = 0; b < nb && e == hipSuccess; ++b) {
         const int64_t start = b * batch, B = (n - start < batch) ? n - start : batch;
-        e = launch_gather_rows(d_x, d_y, perm_d + start, B, xb, yb, s);
-        if (e == hipSuccess)
-          e = launch_mlp_grad(d_theta, d_norm, xb, yb, B, pos_weight, grad,
-                              loss + (b % 4096), work, s);
-        if (e == hipSuccess) e = launch_adam(d_theta, d_m, d_v, grad, ++*step, lr, s);
+        e = launch_mlp_train_step(d_theta, d_m, d_v, d_norm, d_x, d_y, perm_d + start, B,
+                                  pos_weight, ++*step, lr, loss + (b % 4096), work, s);
       }
       // mean batch loss of the epoch (the permutation buffer is reused next epoch)
       if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -279,8 +279,12 @@ hipError_t launch_mlp_grad(const float* theta, const float* norm, const float* X
                            hipStream_t s);
 hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int32_t step, float lr,
                        hipStream_t s);
-hipError_t launch_gather_rows(const float* X, const float* Y, const int32_t* perm, int64_t B,
-                              float* Xb, float* Yb, hipStream_t s);
+// One training step: gradient of the batch rows perm[0 .. B-1] of (X, Y) and
+// the Adam update, the loss into *loss.
+hipError_t launch_mlp_train_step(float* theta, float* m, float* v, const float* norm,
+                                 const float* X, const float* Y, const int32_t* perm, int64_t B,
+                                 float pos_weight, int32_t step, float lr, float* loss, float* work,
+                                 hipStream_t s);
 hipError_t launch_mlp_init(float* theta, unsigned long long seed, hipStream_t s);
 hipError_t launch_features(const float* rec, int64_t n, const double twiss4[4], double emit,
                            double r_ap, const float2* tw, const float* win, float* out,

@@ -11,6 +11,11 @@
 //   A (16 x 16, rows m, cols k): lane l holds A[l % 16][4 (l / 16) + j], j = 0..3
 //   B (16 x 16, rows k, cols n): lane l holds B[4 (l / 16) + j][l % 16]
 //   D (16 x 16):                 lane l holds D[4 (l / 16) + j][l % 16]
+// so the D of a product is, element for element, the B operand of the next
+// one, and the same registers taken as A are the transpose.  Every product
+// below is written in the orientation whose D the next product reads as it
+// lies: activations pass from layer to layer in registers.
+#include <cmath>
 #include <mutex>
 
 #include "xtm_internal.h"
@@ -26,286 +31,399 @@ constexpr int kIn = 16, kH = 128;
 constexpr int oW1 = 0, oB1 = oW1 + kIn * kH, oW2 = oB1 + kH, oB2 = oW2 + kH * kH, oW3 = oB2 + kH,
               oB3 = oW3 + kH, kParams = oB3 + 1;
 static_assert(kParams == 18817, "parameter count");
-constexpr int kSamplesPerBlock = 64;  // 4 waves x 16 samples
+constexpr int kSamplesPerBlock = 64;  // rows of one partial gradient: 4 waves x 16
+constexpr int kTiles = kH / 16;       // 16-neuron tiles of a hidden layer
 
-__device__ __forceinline__ unsigned short to_bf16(float f) {
-  unsigned int u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (unsigned short)((u >> 16) | 0x40u);  // NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (unsigned short)(u >> 16);
+__device__ __forceinline__ float bf16_value(float f) {  // rounded to bf16, as FP32
+  return (float)(__bf16)f;
 }
-__device__ __forceinline__ float from_bf16(unsigned short h) {
-  return __uint_as_float((unsigned int)h << 16);
+__device__ __forceinline__ bf16x4 bf16_pack(float a, float b, float c, float d) {
+  typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+  const b4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
+  return __builtin_bit_cast(bf16x4, v);
+}
+__device__ __forceinline__ float bf16_at(bf16x4 v, int j) {
+  return __uint_as_float((unsigned int)(unsigned short)v[j] << 16);
 }
 __device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
 }
 
-// The network lives in LDS for the whole block: W1 and W2 rounded to BF16
-// once (36 KB), the bias vectors and w3 in FP32.
+// The forward network in LDS, the weights as operand fragments (8 bytes per
+// lane, 64 lanes of a fragment side by side: one conflict-free read each).
+// Lane l of a fragment holds four consecutive k of its column l % 16:
+//   w1[nt][l]      W1[4 q + j][16 nt + l % 16]            (q = l / 16)
+//   w2[nt][kt][l]  W2[16 kt + 4 q + j][16 nt + l % 16]
 struct NetLds {
-  unsigned short w1[kIn * kH];   // bf16 W1[k][n]
-  unsigned short w2[kH * kH];    // bf16 W2[k][n]
+  bf16x4 w1[kTiles][64];
+  bf16x4 w2[kTiles][kTiles][64];
   float b1[kH], b2[kH], w3[kH];  // w3 already rounded to bf16 values
   float b3;
 };
 
 __device__ void load_net(NetLds& s, const float* __restrict__ th) {
-  for (int i = threadIdx.x; i < kIn * kH; i += blockDim.x) s.w1[i] = to_bf16(th[oW1 + i]);
-  for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) s.w2[i] = to_bf16(th[oW2 + i]);
+  // group g: four rows of one column (neighbouring threads neighbouring columns)
+  for (int g = threadIdx.x; g < kIn / 4 * kH; g += blockDim.x) {
+    const int q = g / kH, n = g % kH;
+    const float* w = th + oW1 + 4 * q * kH + n;
+    s.w1[n / 16][q * 16 + n % 16] = bf16_pack(w[0], w[kH], w[2 * kH], w[3 * kH]);
+  }
+#pragma unroll 8
+  for (int g = threadIdx.x; g < kH / 4 * kH; g += blockDim.x) {
+    const int k4 = g / kH, n = g % kH;
+    const float* w = th + oW2 + 4 * k4 * kH + n;
+    s.w2[n / 16][k4 / 4][(k4 % 4) * 16 + n % 16] = bf16_pack(w[0], w[kH], w[2 * kH], w[3 * kH]);
+  }
   for (int i = threadIdx.x; i < kH; i += blockDim.x) {
     s.b1[i] = th[oB1 + i];
     s.b2[i] = th[oB2 + i];
-    s.w3[i] = from_bf16(to_bf16(th[oW3 + i]));
+    s.w3[i] = bf16_value(th[oW3 + i]);
   }
   if (threadIdx.x == 0) s.b3 = th[oB3];
 }
 
-// Forward pass of one wave's 16 samples (rows s0 .. s0+15 of X).  Writes
-// bf16 X, H1, H2 and the ReLU masks (z > 0) for rows r0 .. r0+15 of the
-// block-local arrays, and returns z3 for lane l < 16 (sample s0 + l).
-// The ReLU masks are read back from the activations: bf16(relu(z)) != 0 iff
-// z > 0 (only z below half the smallest bf16 subnormal would differ).
-__device__ float wave_forward(const NetLds& net, const float* __restrict__ X,
-                              const float* __restrict__ norm,
-                              int64_t B, int64_t s0, int r0, unsigned short (*sx)[kIn],
-                              unsigned short (*h1)[kH], unsigned short (*h2)[kH]) {
-  const int l = threadIdx.x & 63;
-  const int row = l & 15, quad = l >> 4;
-  // layer 1 operand: standardised inputs
-  bf16x4 a;
-  for (int j = 0; j < 4; ++j) {
-    const int f = 4 * quad + j;
-    const int64_t s = s0 + row;
-    const float x = (s < B) ? X[s * kIn + f] : 0.0f;
-    const unsigned short v = to_bf16((x - norm[f]) * norm[kIn + f]);
-    a[j] = (short)v;
-    sx[r0 + row][f] = v;
-  }
-  for (int nt = 0; nt < kH / 16; ++nt) {
-    bf16x4 b;
-    for (int j = 0; j < 4; ++j) b[j] = (short)net.w1[(4 * quad + j) * kH + nt * 16 + row];
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    c = mfma16(a, b, c);
-    for (int j = 0; j < 4; ++j) {
-      const int n = nt * 16 + row;
-      const float z = c[j] + net.b1[n];
-      h1[r0 + 4 * quad + j][n] = to_bf16(z > 0.f ? z : 0.f);
-    }
-  }
-  __syncthreads();
-  for (int nt = 0; nt < kH / 16; ++nt) {
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kH / 16; ++kt) {
-      bf16x4 aa, b;
-      for (int j = 0; j < 4; ++j) {
-        aa[j] = (short)h1[r0 + row][kt * 16 + 4 * quad + j];
-        b[j] = (short)net.w2[(kt * 16 + 4 * quad + j) * kH + nt * 16 + row];
-      }
-      c = mfma16(aa, b, c);
-    }
-    for (int j = 0; j < 4; ++j) {
-      const int n = nt * 16 + row;
-      const float z = c[j] + net.b2[n];
-      h2[r0 + 4 * quad + j][n] = to_bf16(z > 0.f ? z : 0.f);
-    }
-  }
-  __syncthreads();
-  float z3 = 0.f;
-  if (l < 16) {
-    float acc = 0.f;
-    for (int k = 0; k < kH; ++k) acc += from_bf16(h2[r0 + l][k]) * net.w3[k];
-    z3 = acc + net.b3;
-  }
-  return z3;
+__device__ __forceinline__ float relu(float z) { return z > 0.f ? z : 0.f; }
+
+// Standardised inputs of row `row` (zeros when `on` is false), features
+// 4 q .. 4 q + 3: the operand of one lane.
+__device__ __forceinline__ bf16x4 load_x(const float* __restrict__ X, int64_t row, bool on, int q,
+                                         const float4& mean, const float4& inv) {
+  const float* r = X + (on ? row : 0) * kIn + 4 * q;
+  const float x0 = on ? r[0] : 0.f, x1 = on ? r[1] : 0.f, x2 = on ? r[2] : 0.f,
+              x3 = on ? r[3] : 0.f;
+  return bf16_pack((x0 - mean.x) * inv.x, (x1 - mean.y) * inv.y, (x2 - mean.z) * inv.z,
+                   (x3 - mean.w) * inv.w);
 }
 
-struct FwdLds {
-  NetLds net;
-  unsigned short x[kSamplesPerBlock][kIn];
-  unsigned short h1[kSamplesPerBlock][kH];
-  unsigned short h2[kSamplesPerBlock][kH];
-};
+__device__ __forceinline__ float4 load4(const float* p) {
+  return make_float4(p[0], p[1], p[2], p[3]);
+}
 
-// Each block loads the network once and then runs 64-sample tiles
-// blockIdx.x, blockIdx.x + gridDim.x, ... (the loop bound is uniform over
-// the block, so every wave meets the same barriers).
+// Activations of four neurons (16 nt + 4 q ..) of one sample: bias, ReLU, bf16.
+__device__ __forceinline__ bf16x4 activate(const f32x4& c, const float* bias) {
+  return bf16_pack(relu(c[0] + bias[0]), relu(c[1] + bias[1]), relu(c[2] + bias[2]),
+                   relu(c[3] + bias[3]));
+}
+
+// Forward pass, T tiles of 16 rows per wave: both layers as weights^T times
+// activations^T, so a layer's D (neurons down, samples across) is the next
+// layer's B operand.  What bounds it: 64 fragment reads of 512 bytes from LDS
+// and 72 T matrix instructions per 16 T rows, and the rows once from HBM;
+// T = 4 shares each fragment read among four products: 84 us for 2^20 rows,
+// 0.47 PFLOP/s, against 760 us, 51 TFLOP/s, when every operand was staged
+// element by element through LDS.  Each block loads the network once and then runs tiles
+// blockIdx.x, blockIdx.x + gridDim.x, ...
+template <int T>
 __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ theta,
                                                      const float* __restrict__ norm,
                                                      const float* __restrict__ X, int64_t B,
                                                      float* __restrict__ logit) {
-  __shared__ FwdLds s;
-  load_net(s.net, theta);
+  __shared__ NetLds net;
+  load_net(net, theta);
   __syncthreads();
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int64_t n_tiles = (B + kSamplesPerBlock - 1) / kSamplesPerBlock;
-  for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
-    const int64_t s0 = t * kSamplesPerBlock + 16 * w;
-    const float z = wave_forward(s.net, X, norm, B, s0, 16 * w, s.x, s.h1, s.h2);
-    if (l < 16 && s0 + l < B) logit[s0 + l] = z;
-    __syncthreads();
+  const int col = l & 15, q = l >> 4;
+  const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
+  const int64_t per_block = 64 * T;
+  for (int64_t base = blockIdx.x * per_block; base < B; base += gridDim.x * per_block) {
+    const int64_t s0 = base + (int64_t)w * 16 * T + col;
+    bf16x4 x[T], h[T][kTiles];
+#pragma unroll
+    for (int t = 0; t < T; ++t) x[t] = load_x(X, s0 + 16 * t, s0 + 16 * t < B, q, mean, inv);
+#pragma unroll
+    for (int nt = 0; nt < kTiles; ++nt) {
+      const bf16x4 a = net.w1[nt][l];
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const f32x4 c = mfma16(a, x[t], f32x4{0.f, 0.f, 0.f, 0.f});
+        h[t][nt] = activate(c, net.b1 + 16 * nt + 4 * q);
+      }
+    }
+    float z[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) z[t] = 0.f;
+#pragma unroll 1
+    for (int nt = 0; nt < kTiles; ++nt) {
+      f32x4 c[T];
+#pragma unroll
+      for (int t = 0; t < T; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kt = 0; kt < kTiles; ++kt) {
+        const bf16x4 a = net.w2[nt][kt][l];
+#pragma unroll
+        for (int t = 0; t < T; ++t) c[t] = mfma16(a, h[t][kt], c[t]);
+      }
+      const float* w3 = net.w3 + 16 * nt + 4 * q;
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const bf16x4 v = activate(c[t], net.b2 + 16 * nt + 4 * q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) z[t] += bf16_at(v, j) * w3[j];
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      float v = z[t];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (q == 0 && s0 + 16 * t < B) logit[s0 + 16 * t] = v + net.b3;
+    }
   }
 }
 
+// Training step of 64 rows per block, 16 per wave, split over gridDim.y blocks
+// that each hold `kTiles / gridDim.y` of the 16-wide column tiles of the weight
+// gradients (every one of them runs the forward pass; a batch of a few
+// thousand rows has fewer 64-row blocks than the chip has CUs).  Operands:
+//   H1^T, H2^T  (D of weights^T x activations^T): B operand of the next layer
+//   H1, dZ2, dZ1 (D of the same registers as A): rows are samples, so they are
+//                operands of the products that contract over samples:
+//                gW2 = H1^T dZ2, gW1 = X^T dZ1
+// H1 and dZ2 of the four waves meet in LDS for gW2's contraction over the
+// block's 64 rows.  What bounds it: latency, a block's chain from the weights
+// (75 KB) over three small products to its share of the partial gradient;
+// 81 us a call of 4,096 rows (16,384: 141) in the form that staged every
+// element through LDS, now 19 (16,384: 40), its reduction included.
 struct GradLds {
   NetLds net;
-  unsigned short x[kSamplesPerBlock][kIn];
-  unsigned short h1[kSamplesPerBlock][kH];
-  unsigned short h2[kSamplesPerBlock][kH];   // H2, then reused for bf16 dZ1
-  unsigned short dz2[kSamplesPerBlock][kH];  // bf16 dZ2
-  float gb1[4][kH];                          // per-wave partial sums of unrounded dZ1
-  float dz3[kSamplesPerBlock];               // unrounded dL/dz3
-  float lossv[kSamplesPerBlock];
+  bf16x4 w2r[kTiles][kTiles][64];   // W2[16 mt + l % 16][16 kt + 4 q + j], own tiles mt
+  bf16x4 h1[4][kTiles][64];         // per wave: H1[4 q + j][16 mt + l % 16]
+  bf16x4 dz2[4][kTiles][64];        // per wave: dZ2[4 q + j][16 nt + l % 16], own tiles nt
+  bf16x4 dz1[4][kTiles][64];        // per wave: dZ1, own tiles
+  unsigned short x[4][16][kIn + 4]; // per wave: rows of X (bf16)
+  float gb1[4][kH], gb2[4][kH], gw3[4][kH];  // per-wave column sums
+  float dz3[4][16], lossv[4][16];
 };
 
-// Per-block partial gradient (mean over the whole batch B) into part[blockIdx][kParams]
-// and the block's summed loss into loss_part[blockIdx].
+// Per-block partial gradient (mean over the whole batch B) into part[blockIdx.x][kParams]
+// and the block's summed loss into loss_part[blockIdx.x].  perm: row r of the
+// batch is row perm[r] of (X, Y); null: row r.
 __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ theta,
                                                   const float* __restrict__ norm,
                                                   const float* __restrict__ X,
-                                                  const float* __restrict__ Y, int64_t B,
+                                                  const float* __restrict__ Y,
+                                                  const int32_t* __restrict__ perm, int64_t B,
                                                   float pos_weight, float* __restrict__ part,
                                                   float* __restrict__ loss_part) {
   __shared__ GradLds s;
-  load_net(s.net, theta);
-  __syncthreads();
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int row = l & 15, quad = l >> 4;
-  const int64_t base = (int64_t)blockIdx.x * kSamplesPerBlock;
-  const int64_t s0 = base + 16 * w;
-  const float z = wave_forward(s.net, X, norm, B, s0, 16 * w, s.x, s.h1, s.h2);
-  if (l < 16) {
-    const int64_t si = s0 + l;
-    float d = 0.f, lv = 0.f;
-    if (si < B) {
-      const float y = Y[si];
-      const float sg = 1.0f / (1.0f + expf(-z));
-      d = (sg * (pos_weight * y + (1.0f - y)) - pos_weight * y) / (float)B;
-      const float lz = log1pf(expf(-fabsf(z)));
-      const float sp_neg = fmaxf(-z, 0.f) + lz, sp_pos = fmaxf(z, 0.f) + lz;
-      lv = pos_weight * y * sp_neg + (1.0f - y) * sp_pos;
+  const int col = l & 15, q = l >> 4;
+  const int own = kTiles / (int)gridDim.y, t0 = (int)blockIdx.y * own;  // own tiles t0 .. t0 + own
+  load_net(s.net, theta);
+  for (int g = threadIdx.x; g < own * 16 * (kH / 4); g += blockDim.x) {
+    const int r = t0 * 16 + g / (kH / 4), c4 = g % (kH / 4);
+    const float4 v = load4(theta + oW2 + r * kH + 4 * c4);
+    s.w2r[r / 16][c4 / 4][(c4 % 4) * 16 + r % 16] = bf16_pack(v.x, v.y, v.z, v.w);
+  }
+  const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
+  const int64_t row = (int64_t)blockIdx.x * kSamplesPerBlock + 16 * w + col;  // this lane's sample
+  const bool on = row < B;
+  const int64_t src = on ? (perm ? perm[row] : row) : 0;
+  const bf16x4 x = load_x(X, src, on, q, mean, inv);
+  *reinterpret_cast<bf16x4*>(&s.x[w][col][4 * q]) = x;
+  const float y = on ? Y[src] : 0.f;
+  __syncthreads();
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  bf16x4 h1t[kTiles];
+#pragma unroll
+  for (int nt = 0; nt < kTiles; ++nt) {
+    const bf16x4 a = s.net.w1[nt][l];
+    h1t[nt] = activate(mfma16(a, x, zero), s.net.b1 + 16 * nt + 4 * q);
+    const f32x4 c = mfma16(x, a, zero);  // samples down, neurons across
+    const float b = s.net.b1[16 * nt + col];
+    s.h1[w][nt][l] =
+        bf16_pack(relu(c[0] + b), relu(c[1] + b), relu(c[2] + b), relu(c[3] + b));
+  }
+  float z = 0.f;
+  bf16x4 h2t[kTiles];
+#pragma unroll
+  for (int nt = 0; nt < kTiles; ++nt) {
+    f32x4 c = zero;
+#pragma unroll
+    for (int kt = 0; kt < kTiles; ++kt) c = mfma16(s.net.w2[nt][kt][l], h1t[kt], c);
+    h2t[nt] = activate(c, s.net.b2 + 16 * nt + 4 * q);
+    const float* w3 = s.net.w3 + 16 * nt + 4 * q;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z += bf16_at(h2t[nt], j) * w3[j];
+  }
+  z += __shfl_xor(z, 16, 64);
+  z += __shfl_xor(z, 32, 64);
+  z += s.net.b3;
+  // dL/dz3 of this lane's sample (the four quads hold the same)
+  float d = 0.f, lv = 0.f;
+  if (on) {
+    const float sg = 1.0f / (1.0f + expf(-z));
+    d = (sg * (pos_weight * y + (1.0f - y)) - pos_weight * y) / (float)B;
+    const float lz = log1pf(expf(-fabsf(z)));
+    const float sp_neg = fmaxf(-z, 0.f) + lz, sp_pos = fmaxf(z, 0.f) + lz;
+    lv = pos_weight * y * sp_neg + (1.0f - y) * sp_pos;
+  }
+  if (q == 0) {
+    s.dz3[w][col] = d;
+    s.lossv[w][col] = lv;
+  }
+  __syncthreads();
+  const float dq = bf16_value(d);  // this lane's sample across
+  float dqr[4];                    // the four samples down
+#pragma unroll
+  for (int j = 0; j < 4; ++j) dqr[j] = bf16_value(s.dz3[w][4 * q + j]);
+  // dZ2 transposed: the operand of dH1 = dZ2 W2^T
+  bf16x4 dz2t[kTiles];
+#pragma unroll
+  for (int nt = 0; nt < kTiles; ++nt) {
+    const float* w3 = s.net.w3 + 16 * nt + 4 * q;
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = bf16_at(h2t[nt], j) > 0.f ? dq * w3[j] : 0.f;
+    dz2t[nt] = bf16_pack(v[0], v[1], v[2], v[3]);
+  }
+  // own tiles, samples down: H2, dZ2 (with the b2 and w3 sums), dZ1 (with b1's)
+  for (int nt = t0; nt < t0 + own; ++nt) {
+    const int n = 16 * nt + col;
+    f32x4 c = zero;
+#pragma unroll
+    for (int kt = 0; kt < kTiles; ++kt) c = mfma16(h1t[kt], s.net.w2[nt][kt][l], c);
+    const float b = s.net.b2[n], w3 = s.net.w3[n];
+    float v[4], gb2 = 0.f, gw3 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float h = bf16_value(relu(c[j] + b));
+      v[j] = h > 0.f ? dqr[j] * w3 : 0.f;
+      gb2 += v[j];
+      gw3 += h * dqr[j];
     }
-    s.dz3[16 * w + l] = d;
-    s.lossv[16 * w + l] = lv;
+    s.dz2[w][nt][l] = bf16_pack(v[0], v[1], v[2], v[3]);
+    f32x4 g = zero;
+#pragma unroll
+    for (int kt = 0; kt < kTiles; ++kt) g = mfma16(dz2t[kt], s.w2r[nt][kt][l], g);
+    const bf16x4 h1 = s.h1[w][nt][l];
+    float gb1 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = bf16_at(h1, j) > 0.f ? g[j] : 0.f;
+      gb1 += v[j];
+    }
+    s.dz1[w][nt][l] = bf16_pack(v[0], v[1], v[2], v[3]);
+    gb1 += __shfl_xor(gb1, 16, 64);
+    gb1 += __shfl_xor(gb1, 32, 64);
+    gb2 += __shfl_xor(gb2, 16, 64);
+    gb2 += __shfl_xor(gb2, 32, 64);
+    gw3 += __shfl_xor(gw3, 16, 64);
+    gw3 += __shfl_xor(gw3, 32, 64);
+    if (q == 0) {
+      s.gb1[w][n] = gb1;
+      s.gb2[w][n] = gb2;
+      s.gw3[w][n] = gw3;
+    }
   }
   __syncthreads();
   float* g = part + (size_t)blockIdx.x * kParams;
-  // dZ2 = bf16(dz3) bf16(w3) masked; b2, w3, b3 partial sums (fixed order)
-  for (int n = threadIdx.x; n < kH; n += blockDim.x) {
-    float gb2 = 0.f, gw3 = 0.f;
-    for (int r = 0; r < kSamplesPerBlock; ++r) {
-      const float dq = from_bf16(to_bf16(s.dz3[r]));
-      const float d2 = s.h2[r][n] ? dq * s.net.w3[n] : 0.f;
-      s.dz2[r][n] = to_bf16(d2);
-      gb2 += d2;
-      gw3 += from_bf16(s.h2[r][n]) * dq;
-    }
-    g[oB2 + n] = gb2;
-    g[oW3 + n] = gw3;
-  }
-  if (threadIdx.x == 0) {
-    float gb3 = 0.f, ls = 0.f;
-    for (int r = 0; r < kSamplesPerBlock; ++r) {
-      gb3 += s.dz3[r];
-      ls += s.lossv[r];
-    }
-    g[oB3] = gb3;
-    loss_part[blockIdx.x] = ls;
-  }
-  __syncthreads();
-  // dH1 = bf16(dZ2) bf16(W2)^T per wave; dZ1 = dH1 masked (mask from H1),
-  // stored as bf16 in the H2 slot; unrounded column sums give the b1 partial
-  for (int nt = 0; nt < kH / 16; ++nt) {
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kH / 16; ++kt) {
-      bf16x4 a, b;
-      for (int j = 0; j < 4; ++j) {
-        a[j] = (short)s.dz2[16 * w + row][kt * 16 + 4 * quad + j];
-        b[j] = (short)s.net.w2[(nt * 16 + row) * kH + kt * 16 + 4 * quad + j];
-      }
-      c = mfma16(a, b, c);
-    }
-    float colsum = 0.f;
-    for (int j = 0; j < 4; ++j) {
-      const int r = 16 * w + 4 * quad + j, n = nt * 16 + row;
-      const float d1 = s.h1[r][n] ? c[j] : 0.f;
-      s.h2[r][n] = to_bf16(d1);
-      colsum += d1;
-    }
-    // lanes l, l^16, l^32, l^48 hold the same column: fixed-order combine
-    colsum += __shfl_xor(colsum, 16, 64);
-    colsum += __shfl_xor(colsum, 32, 64);
-    if (quad == 0) s.gb1[w][nt * 16 + row] = colsum;
-  }
-  __syncthreads();
-  for (int n = threadIdx.x; n < kH; n += blockDim.x)
+  for (int n = 16 * t0 + (int)threadIdx.x; n < 16 * (t0 + own); n += blockDim.x) {
     g[oB1 + n] = ((s.gb1[0][n] + s.gb1[1][n]) + s.gb1[2][n]) + s.gb1[3][n];
-  // weight gradients with K = samples of the block (4 k-steps of 16)
-  // W2[j1][n2] = sum_s H1[s][j1] dZ2[s][n2]: 64 output tiles, 16 per wave
-  for (int t = w; t < 64; t += 4) {
-    const int mt = t >> 3, nt = t & 7;
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kSamplesPerBlock / 16; ++kt) {
-      bf16x4 a, b;
-      for (int j = 0; j < 4; ++j) {
-        a[j] = (short)s.h1[kt * 16 + 4 * quad + j][mt * 16 + row];
-        b[j] = (short)s.dz2[kt * 16 + 4 * quad + j][nt * 16 + row];
-      }
-      c = mfma16(a, b, c);
-    }
-    for (int j = 0; j < 4; ++j) g[oW2 + (mt * 16 + 4 * quad + j) * kH + nt * 16 + row] = c[j];
+    g[oB2 + n] = ((s.gb2[0][n] + s.gb2[1][n]) + s.gb2[2][n]) + s.gb2[3][n];
+    g[oW3 + n] = ((s.gw3[0][n] + s.gw3[1][n]) + s.gw3[2][n]) + s.gw3[3][n];
   }
-  // W1[f][j1] = sum_s X[s][f] dZ1[s][j1]: 8 output tiles, 2 per wave
-  for (int nt = w; nt < 8; nt += 4) {
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < kSamplesPerBlock / 16; ++kt) {
-      bf16x4 a, b;
-      for (int j = 0; j < 4; ++j) {
-        a[j] = (short)s.x[kt * 16 + 4 * quad + j][row];
-        b[j] = (short)s.h2[kt * 16 + 4 * quad + j][nt * 16 + row];   // bf16 dZ1
-      }
-      c = mfma16(a, b, c);
+  if (w == 0 && blockIdx.y == 0) {  // lanes 0..63: the block's samples
+    float gb3 = s.dz3[q][col], ls = s.lossv[q][col];
+    for (int o = 32; o > 0; o >>= 1) {
+      gb3 += __shfl_xor(gb3, o, 64);
+      ls += __shfl_xor(ls, o, 64);
     }
-    for (int j = 0; j < 4; ++j) g[oW1 + (4 * quad + j) * kH + nt * 16 + row] = c[j];
+    if (l == 0) {
+      g[oB3] = gb3;
+      loss_part[blockIdx.x] = ls;
+    }
+  }
+  // W2[j1][n2] = sum_s H1[s][j1] dZ2[s][n2], own n2 tiles, in steps of 16 rows
+  for (int t = w; t < kTiles * own; t += 4) {
+    const int mt = t % kTiles, nt = t0 + t / kTiles;
+    f32x4 c = zero;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) c = mfma16(s.h1[kt][mt][l], s.dz2[kt][nt][l], c);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[oW2 + (mt * 16 + 4 * q + j) * kH + nt * 16 + col] = c[j];
+  }
+  // W1[f][j1] = sum_s X[s][f] dZ1[s][j1], own j1 tiles
+  for (int nt = t0 + w; nt < t0 + own; nt += 4) {
+    f32x4 c = zero;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt) {
+      bf16x4 a;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[j] = (short)s.x[kt][4 * q + j][col];
+      c = mfma16(a, s.dz1[kt][nt][l], c);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) g[oW1 + (4 * q + j) * kH + nt * 16 + col] = c[j];
   }
 }
 
-// grad[i] = sum over blocks b = 0..nb-1 (in order) of part[b][i]; loss likewise.
-__global__ void __launch_bounds__(256) k_mlp_reduce(const float* __restrict__ part, int nb,
-                                                    const float* __restrict__ loss_part,
-                                                    float* __restrict__ grad,
-                                                    float* __restrict__ loss, int64_t B) {
+// Sum over blocks b = 0..nb-1 (in order) of part[b][i]: the loads of sixteen
+// partials in flight at a time (the sums of one parameter are one chain).
+__device__ __forceinline__ float sum_parts(const float* __restrict__ part, int nb, size_t stride,
+                                           int i) {
+  float acc = 0.f;
+  int b = 0;
+  for (; b + 16 <= nb; b += 16) {
+    float v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = part[(size_t)(b + k) * stride + i];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc += v[k];
+  }
+  for (; b < nb; ++b) acc += part[(size_t)b * stride + i];
+  return acc;
+}
+
+__global__ void __launch_bounds__(64) k_mlp_reduce(const float* __restrict__ part, int nb,
+                                                   const float* __restrict__ loss_part,
+                                                   float* __restrict__ grad,
+                                                   float* __restrict__ loss, int64_t B) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kParams) {
-    float acc = 0.f;
-    for (int b = 0; b < nb; ++b) acc += part[(size_t)b * kParams + i];
-    grad[i] = acc;
-  }
-  if (i == 0 && loss) {
-    float acc = 0.f;
-    for (int b = 0; b < nb; ++b) acc += loss_part[b];
-    *loss = acc / (float)B;
-  }
+  if (i < kParams) grad[i] = sum_parts(part, nb, kParams, i);
+  if (i == kParams && loss) *loss = sum_parts(loss_part, nb, 1, 0) / (float)B;
 }
 
 // Adam (Kingma & Ba): m <- b1 m + (1-b1) g, v <- b2 v + (1-b2) g^2,
-// theta <- theta - lr mhat / (sqrt(vhat) + eps), bias-corrected with step t >= 1.
-// The update is evaluated in FP64 from the FP32 masters and moments (b1 = 0.9,
-// b2 = 0.999 exactly, not their FP32 roundings) and stored back in FP32.
-__global__ void __launch_bounds__(256) k_adam(float* __restrict__ theta, float* __restrict__ m,
-                                              float* __restrict__ v,
-                                              const float* __restrict__ grad, int step, float lr,
-                                              double b1, double b2, double eps) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kParams) return;
-  const double g = grad[i];
-  const double mi = b1 * (double)m[i] + (1.0 - b1) * g;
-  const double vi = b2 * (double)v[i] + (1.0 - b2) * g * g;
+// theta <- theta - lr mhat / (sqrt(vhat) + eps), bias-corrected with step t >= 1
+// (c1 = 1 - b1^t, c2 = 1 - b2^t, from the host).  The update is evaluated in
+// FP64 from the FP32 masters and moments (b1 = 0.9, b2 = 0.999 exactly, not
+// their FP32 roundings) and stored back in FP32.
+struct AdamStep {
+  double b1, b2, eps, c1, c2;
+  float lr;
+};
+
+__device__ __forceinline__ void adam_update(float* __restrict__ theta, float* __restrict__ m,
+                                            float* __restrict__ v, int i, double g,
+                                            const AdamStep& a) {
+  const double mi = a.b1 * (double)m[i] + (1.0 - a.b1) * g;
+  const double vi = a.b2 * (double)v[i] + (1.0 - a.b2) * g * g;
   m[i] = (float)mi;
   v[i] = (float)vi;
-  const double mh = mi / (1.0 - pow(b1, (double)step));
-  const double vh = vi / (1.0 - pow(b2, (double)step));
-  theta[i] = (float)((double)theta[i] - (double)lr * mh / (sqrt(vh) + eps));
+  const double mh = mi / a.c1;
+  const double vh = vi / a.c2;
+  theta[i] = (float)((double)theta[i] - (double)a.lr * mh / (sqrt(vh) + a.eps));
+}
+
+__global__ void __launch_bounds__(64) k_adam(float* __restrict__ theta, float* __restrict__ m,
+                                             float* __restrict__ v,
+                                             const float* __restrict__ grad, AdamStep a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kParams) adam_update(theta, m, v, i, grad[i], a);
+}
+
+// The reduction of a training step and its update in one launch (the training
+// loop keeps no gradient).
+__global__ void __launch_bounds__(64) k_mlp_reduce_adam(const float* __restrict__ part, int nb,
+                                                        const float* __restrict__ loss_part,
+                                                        float* __restrict__ loss, int64_t B,
+                                                        float* __restrict__ theta,
+                                                        float* __restrict__ m,
+                                                        float* __restrict__ v, AdamStep a) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kParams) adam_update(theta, m, v, i, sum_parts(part, nb, kParams, i), a);
+  if (i == kParams && loss) *loss = sum_parts(loss_part, nb, 1, 0) / (float)B;
 }
 
 // He-normal initialisation: weights std sqrt(2/fan_in) times the Philox
@@ -583,36 +701,22 @@ __global__ void __launch_bounds__(256) k_rule_score(const float* __restrict__ f,
   score[i] = (a != a || b != b) ? __builtin_nanf("") : -(a > b ? a : b);
 }
 
-// Rows perm[start .. start+B-1] of (X, Y) into the contiguous batch (Xb, Yb).
-__global__ void __launch_bounds__(256) k_gather_rows(const float* __restrict__ X,
-                                                     const float* __restrict__ Y,
-                                                     const int32_t* __restrict__ perm,
-                                                     int64_t B, float* __restrict__ Xb,
-                                                     float* __restrict__ Yb) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= B * kIn) return;
-  const int64_t r = i / kIn, f = i - r * kIn;
-  const int64_t src = perm[r];
-  Xb[i] = X[src * kIn + f];
-  if (f == 0) Yb[r] = Y[src];
-}
-
 // ------------------------------------------------------------- launchers
-hipError_t launch_gather_rows(const float* X, const float* Y, const int32_t* perm, int64_t B,
-                              float* Xb, float* Yb, hipStream_t s) {
-  if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_rows, dim3((unsigned)((B * kIn + 255) / 256)), dim3(256), 0, s, X, Y,
-                     perm, B, Xb, Yb);
-  return hipGetLastError();
-}
-
 hipError_t launch_mlp_forward(const float* theta, const float* norm, const float* X, int64_t B,
                               float* logit, hipStream_t s) {
   if (B <= 0) return hipSuccess;
-  // at most two blocks per compute unit: each loads the network once
-  const int64_t tiles = (B + kSamplesPerBlock - 1) / kSamplesPerBlock;
-  const unsigned nb = (unsigned)(tiles < 512 ? tiles : 512);
-  hipLaunchKernelGGL(k_mlp_forward, dim3(nb), dim3(256), 0, s, theta, norm, X, B, logit);
+  // four tiles a wave once that still gives every CU a block (2^16 rows: 256
+  // blocks), one before; at most four blocks per CU, each of which loads the
+  // network once.  us for 16,384 / 2^17 / 2^20 rows: 13 / 17 / 88 (a call; 29 /
+  // 108 / 757 with one block per 64 rows and the staging of every operand).
+  if (B >= 65536) {
+    const int64_t nb = (B + 255) / 256;
+    hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s,
+                       theta, norm, X, B, logit);
+  } else {
+    hipLaunchKernelGGL(k_mlp_forward<1>, dim3((unsigned)((B + 63) / 64)), dim3(256), 0, s, theta,
+                       norm, X, B, logit);
+  }
   return hipGetLastError();
 }
 
@@ -652,26 +756,59 @@ hipError_t mlp_noalloc_workspace(float** out) {
   return hipSuccess;
 }
 
+namespace {
+// column splits of a 64-row block: as many as keep the launch within one block
+// per CU (256), of 1, 2, 4
+unsigned grad_split(int64_t nb) { return nb <= 64 ? 4u : (nb <= 128 ? 2u : 1u); }
+
+void enqueue_grad(const float* theta, const float* norm, const float* X, const float* Y,
+                  const int32_t* perm, int64_t B, float pos_weight, float* work, hipStream_t s) {
+  const int64_t nb = (B + kSamplesPerBlock - 1) / kSamplesPerBlock;
+  hipLaunchKernelGGL(k_mlp_grad, dim3((unsigned)nb, grad_split(nb)), dim3(256), 0, s, theta, norm,
+                     X, Y, perm, B, pos_weight, work, work + (size_t)nb * kParams);
+}
+
+AdamStep adam_step(int32_t step, float lr) {
+  AdamStep a{0.9, 0.999, 1e-8, 0.0, 0.0, lr};
+  a.c1 = 1.0 - std::pow(a.b1, (double)step);
+  a.c2 = 1.0 - std::pow(a.b2, (double)step);
+  return a;
+}
+
+constexpr unsigned kParamBlocks = (kParams + 1 + 63) / 64;  // one thread more: the loss
+}  // namespace
+
 hipError_t launch_mlp_grad(const float* theta, const float* norm, const float* X, const float* Y,
                            int64_t B, float pos_weight, float* grad, float* loss, float* work,
                            hipStream_t s) {
   if (B <= 0) return hipSuccess;
   const int nb = (int)((B + kSamplesPerBlock - 1) / kSamplesPerBlock);
-  float* part = work;
-  float* lpart = work + (size_t)nb * kParams;
-  hipLaunchKernelGGL(k_mlp_grad, dim3(nb), dim3(256), 0, s, theta, norm, X, Y, B, pos_weight,
-                     part, lpart);
+  enqueue_grad(theta, norm, X, Y, nullptr, B, pos_weight, work, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kParams + 255) / 256), dim3(256), 0, s, part, nb, lpart,
-                     grad, loss, B);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(kParamBlocks), dim3(64), 0, s, work, nb,
+                     work + (size_t)nb * kParams, grad, loss, B);
   return hipGetLastError();
 }
 
 hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int32_t step, float lr,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_adam, dim3((kParams + 255) / 256), dim3(256), 0, s, theta, m, v, grad, step,
-                     lr, 0.9, 0.999, 1e-8);
+  hipLaunchKernelGGL(k_adam, dim3(kParamBlocks), dim3(64), 0, s, theta, m, v, grad,
+                     adam_step(step, lr));
+  return hipGetLastError();
+}
+
+hipError_t launch_mlp_train_step(float* theta, float* m, float* v, const float* norm,
+                                 const float* X, const float* Y, const int32_t* perm, int64_t B,
+                                 float pos_weight, int32_t step, float lr, float* loss, float* work,
+                                 hipStream_t s) {
+  if (B <= 0) return hipSuccess;
+  const int nb = (int)((B + kSamplesPerBlock - 1) / kSamplesPerBlock);
+  enqueue_grad(theta, norm, X, Y, perm, B, pos_weight, work, s);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kParamBlocks), dim3(64), 0, s, work, nb,
+                     work + (size_t)nb * kParams, loss, B, theta, m, v, adam_step(step, lr));
   return hipGetLastError();
 }
 
