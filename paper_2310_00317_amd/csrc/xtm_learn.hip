@@ -442,219 +442,349 @@ __global__ void __launch_bounds__(256) k_mlp_init(float* __restrict__ theta,
 // ------------------------------------------------------------- features
 constexpr int kWin = 512, kRecTurns = 1024;
 
-__device__ __forceinline__ int rev9(int v) { return (int)(__brev((unsigned)v) >> 23); }
+// x / b with r = 1/b rounded: product, exact remainder and correction instead
+// of the division's eleven operations (an infinite quotient stays one).
+__device__ __forceinline__ double div_by(double x, double b, double r) {
+  const double q = x * r;
+  const double c = fma(fma(-b, q, x), r, q);
+  return isinf(q) ? q : c;
+}
 
+// Three stages (half = stride, 2 stride, 4 stride) of the radix-2
+// decimation-in-time transform on eight elements `stride` apart, the first of
+// them at position `pos` of its group of `stride`: v0 +- w v1 with
+// w = exp(-i 2 pi k / 512) = (cos, -sin) from tw.
+template <int kStride>
+__device__ __forceinline__ void fft_stages(float2 (&v)[8], int pos, const float2* tw) {
+#pragma unroll
+  for (int st = 0; st < 3; ++st) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (k & (1 << st)) continue;
+      const int low = k & ((1 << st) - 1);
+      const float2 w = tw[(pos + kStride * low) * (256 / (kStride << st))];
+      const float2 v0 = v[k], v1 = v[k | (1 << st)];
+      const float tr = w.x * v1.x + w.y * v1.y;
+      const float ti = w.x * v1.y - w.y * v1.x;
+      v[k | (1 << st)] = make_float2(v0.x - tr, v0.y - ti);
+      v[k] = make_float2(v0.x + tr, v0.y + ti);
+    }
+  }
+}
+
+// G particles per workgroup of T threads: thread % G is the particle, and T / G
+// threads share its turns.
+constexpr int kStats = 10;
+template <int G, int T>
 struct FeatLds {
-  float2 z[4][kWin];  // x first half, y first half, x second half, y second half
-  double jx[kRecTurns], jy[kRecTurns];
-  double red[256];
-  float fred[256];
-  int ired[256];
+  float2 z[kWin][G];  // one transform of each particle
+  float2 tw[kWin / 2];
+  float win[kWin];
+  double red[T / 64][kStats][G];
+  float best[T / 64][G];
+  int at[T / 64][G];
 };
 
-__device__ double block_sum(double v, double* buf) {
-  buf[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) buf[threadIdx.x] += buf[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = buf[0];
-  __syncthreads();
-  return r;
+template <int G>
+__device__ __forceinline__ double lanes_sum(double v) {
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <int G>
+__device__ __forceinline__ double lanes_max(double v) {
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  return v;
 }
 
-__device__ double block_max(double v, double* buf) {
-  buf[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) buf[threadIdx.x] = fmax(buf[threadIdx.x], buf[threadIdx.x + s]);
-    __syncthreads();
+// Second and third pass over the transform in s.z, then the peak bin (first
+// index on ties) and Hann's three-point interpolation: ((k + d) / 512) mod 1
+// for the threads below G.
+template <int G, int T>
+__device__ float tune_of(FeatLds<G, T>& s) {
+  constexpr int kThreads = T / G;
+  const int p = threadIdx.x % G;
+  // (hidden from the optimiser, which would otherwise keep the twiddles of
+  // every pass in registers from one transform to the next)
+  int tl = threadIdx.x / G;
+  asm volatile("" : "+v"(tl));
+#pragma unroll
+  for (int i = tl; i < kWin / 8; i += kThreads) {
+    float2 v[8];
+    const int base = (i / 8) * 64 + i % 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = s.z[base + 8 * j][p];
+    fft_stages<8>(v, i % 8, s.tw);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s.z[base + 8 * j][p] = v[j];
   }
-  const double r = buf[0];
   __syncthreads();
-  return r;
-}
-
-// Argmax of |z[a][k]| over k (first index on ties), then the Hann three-point
-// interpolation; returns ((k + d) / 512) mod 1.
-__device__ float tune_of(FeatLds& s, int a) {
   float best = -1.f;
-  int bi = 0;
-  for (int k = threadIdx.x; k < kWin; k += blockDim.x) {
-    const float2 v = s.z[a][k];
-    const float m = sqrtf(v.x * v.x + v.y * v.y);
-    if (m > best) {
-      best = m;
-      bi = k;
-    }
-  }
-  s.fred[threadIdx.x] = best;
-  s.ired[threadIdx.x] = bi;
-  __syncthreads();
-  for (int st = blockDim.x / 2; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) {
-      const float o = s.fred[threadIdx.x + st];
-      const int oi = s.ired[threadIdx.x + st];
-      if (o > s.fred[threadIdx.x] || (o == s.fred[threadIdx.x] && oi < s.ired[threadIdx.x])) {
-        s.fred[threadIdx.x] = o;
-        s.ired[threadIdx.x] = oi;
+  int at = 0;
+#pragma unroll
+  for (int i = tl; i < kWin / 8; i += kThreads) {
+    float2 v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = s.z[i + 64 * j][p];
+    fft_stages<64>(v, i, s.tw);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int k = i + 64 * j;
+      const float m = sqrtf(v[j].x * v[j].x + v[j].y * v[j].y);
+      s.z[k][p].x = m;
+      if (m > best || (m == best && k < at)) {
+        best = m;
+        at = k;
       }
     }
-    __syncthreads();
   }
-  const int k = s.ired[0];
+#pragma unroll
+  for (int o = G; o < 64; o <<= 1) {
+    const float ob = __shfl_xor(best, o, 64);
+    const int oa = __shfl_xor(at, o, 64);
+    if (ob > best || (ob == best && oa < at)) {
+      best = ob;
+      at = oa;
+    }
+  }
+  if ((threadIdx.x & 63) < G) {
+    s.best[threadIdx.x >> 6][p] = best;
+    s.at[threadIdx.x >> 6][p] = at;
+  }
   __syncthreads();
-  auto mag = [&](int kk) {
-    const float2 v = s.z[a][(kk + kWin) % kWin];
-    return sqrtf(v.x * v.x + v.y * v.y);
-  };
-  const float am = mag(k - 1), b = mag(k), c = mag(k + 1);
-  const float d = 2.0f * (c - am) / (am + 2.0f * b + c);
-  float q = ((float)k + d) / (float)kWin;
-  q = q - floorf(q);
+  float q = 0.f;
+  if (threadIdx.x < G) {
+    for (int w = 1; w < T / 64; ++w) {
+      const float ob = s.best[w][p];
+      const int oa = s.at[w][p];
+      if (ob > best || (ob == best && oa < at)) {
+        best = ob;
+        at = oa;
+      }
+    }
+    const float am = s.z[(at + kWin - 1) % kWin][p].x, b = s.z[at][p].x,
+                c = s.z[(at + 1) % kWin][p].x;
+    const float d = 2.0f * (c - am) / (am + 2.0f * b + c);
+    q = ((float)at + d) / (float)kWin;
+    q = q - floorf(q);
+  }
+  __syncthreads();
   return q;
 }
 
-// One workgroup of 256 per particle: record [1024][4][n] (x, px, y, py at
-// element 0 at the start of each turn) -> 16 features (definitions in
-// include/xtm.h).  The action statistics are taken in FP64 from the FP32
-// record (two passes for the spread); the spectra are FP32 FFTs.
+// Record [1024][4][n] (x, px, y, py at element 0 at the start of each turn)
+// -> 16 features (definitions in include/xtm.h).  The action statistics are
+// taken in FP64 from the FP32 record (sums of the differences from the first
+// turn's action: one pass, no cancellation); the spectra are FP32 FFTs.
 // tw[k] = (cos, sin)(2 pi k / 512) for k < 256, win[n] = sin^2(pi n / 512).
-__global__ void __launch_bounds__(256) k_features(const float* __restrict__ rec, int64_t n,
+//   What bounds it: the record is read once, 16 KB per particle; a turn of one
+// particle is 4 bytes in a row of n, so G = 8 neighbours share each 32-byte
+// piece, and groups of neighbours are numbered within an XCD (blocks go round
+// the eight XCDs), whose L2 then holds the rest of each 128-byte line.
+// One particle per workgroup fetched every piece eight times over: 1,040 us
+// for 20,000 particles, 0.32 TB/s; now 192 us, 1.7 TB/s, the rest of the
+// time being the FP64 actions and the transforms between the barriers.  Eight
+// butterflies' elements stay in registers for three stages, so a transform
+// crosses LDS three times, not nine (same operations in the same order).
+// Off: the type of a lane's offset within 64 turns (32 bits while 64 rows of
+// 4 n floats stay below 4 GiB).
+template <int G, int T, typename Off>
+__global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec, int64_t n,
                                                   double bx, double ax, double by, double ay,
                                                   double emit, double r_ap,
                                                   const float2* __restrict__ tw,
                                                   const float* __restrict__ win,
                                                   float* __restrict__ out) {
-  __shared__ FeatLds s;
-  const int64_t p = blockIdx.x;
-  if (p >= n) return;
-  const double sbx = sqrt(bx), sby = sqrt(by);
-  double rmax = 0.0, amax = 0.0;
-  for (int t = threadIdx.x; t < kRecTurns; t += blockDim.x) {
-    const double x = rec[((size_t)t * 4 + 0) * n + p], px = rec[((size_t)t * 4 + 1) * n + p];
-    const double y = rec[((size_t)t * 4 + 2) * n + p], py = rec[((size_t)t * 4 + 3) * n + p];
-    const double ux = x / sbx, pux = (ax * x + bx * px) / sbx;
-    const double uy = y / sby, puy = (ay * y + by * py) / sby;
-    const double jx = 0.5 * (ux * ux + pux * pux), jy = 0.5 * (uy * uy + puy * puy);
-    s.jx[t] = jx;
-    s.jy[t] = jy;
-    rmax = fmax(rmax, sqrt(x * x + y * y));
-    amax = fmax(amax, 2.0 * (jx + jy) / emit);
-    const int h = t >= kWin, tt = t - h * kWin;
-    const float wv = win[tt];
-    s.z[2 * h + 0][rev9(tt)] = make_float2(wv * (float)ux, -wv * (float)pux);
-    s.z[2 * h + 1][rev9(tt)] = make_float2(wv * (float)uy, -wv * (float)puy);
-  }
+  __shared__ FeatLds<G, T> s;
+  constexpr int kThreads = T / G, kBlk = 64 / kThreads;
+  const int64_t groups = (n + G - 1) / G, per_xcd = (groups + 7) / 8;
+  const int64_t grp = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (grp >= groups) return;
+  const int p = threadIdx.x % G, tl = threadIdx.x / G;
+  const int64_t i = grp * G + p;
+  const bool on = i < n;
+  const int64_t ip = on ? i : n - 1;
+  const float* __restrict__ r = rec + ip;
+  for (int k = threadIdx.x; k < kWin / 2; k += T) s.tw[k] = tw[k];
+  for (int k = threadIdx.x; k < kWin; k += T) s.win[k] = win[k];
+  const double sbx = sqrt(bx), sby = sqrt(by), rsx = 1.0 / sbx, rsy = 1.0 / sby;
+  auto action = [](double x, double px, double a, double b, double sb, double rs, double& u,
+                   double& pu) {
+    u = div_by(x, sb, rs);
+    pu = div_by(a * x + b * px, sb, rs);
+    return 0.5 * (u * u + pu * pu);
+  };
+  double u, pu;
+  const double jx0 = action(r[0], r[n], ax, bx, sbx, rsx, u, pu);
+  const double jy0 = action(r[2 * n], r[3 * n], ay, by, sby, rsy, u, pu);
+  // sums of j - j0 and its square, the first and last quarter's j; maxima
+  double d1x = 0.0, d2x = 0.0, f0x = 0.0, f1x = 0.0, d1y = 0.0, d2y = 0.0, f0y = 0.0, f1y = 0.0;
+  double r2max = 0.0, amax = 0.0;
+  float q[4];
   __syncthreads();
-  // radix-2 decimation-in-time FFT, 4 transforms x 256 butterflies per stage
-  for (int half = 1; half < kWin; half <<= 1) {
-    for (int task = threadIdx.x; task < 4 * (kWin / 2); task += blockDim.x) {
-      const int a = task / (kWin / 2), bfly = task % (kWin / 2);
-      const int grp = bfly / half, pos = bfly % half;
-      const int i0 = grp * 2 * half + pos, i1 = i0 + half;
-      const float2 wt = tw[pos * (kWin / 2 / half)];   // exp(-i 2 pi k / 512) = (cos, -sin)
-      const float2 v1 = s.z[a][i1], v0 = s.z[a][i0];
-      const float tr = wt.x * v1.x + wt.y * v1.y;
-      const float ti = wt.x * v1.y - wt.y * v1.x;
-      s.z[a][i1] = make_float2(v0.x - tr, v0.y - ti);
-      s.z[a][i0] = make_float2(v0.x + tr, v0.y + ti);
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    float2 zy[kBlk][8];
+#pragma unroll
+    for (int b = 0; b < kBlk; ++b) {
+      // elements 8 blk .. 8 blk + 7 of the bit-reversed order: turns 64 apart
+      const int blk = tl + kThreads * b;
+      const int tb = (int)(__brev((unsigned)blk) >> 26);
+      float2 zx[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int rk = ((k & 1) << 2) | (k & 2) | (k >> 2), t = tb + 64 * rk;
+        // a row common to the workgroup, and the lane's offset from it
+        const float* __restrict__ row = rec + (size_t)(h * kWin + 64 * rk) * 4 * n;
+        const Off at = (Off)tb * 4 * (Off)n + (Off)ip;
+        const double x = row[at], px = row[n + at], y = row[2 * n + at], py = row[3 * n + at];
+        double ux, pux, uy, puy;
+        const double jx = action(x, px, ax, bx, sbx, rsx, ux, pux);
+        const double jy = action(y, py, ay, by, sby, rsy, uy, puy);
+        const double dx = jx - jx0, dy = jy - jy0;
+        d1x += dx;
+        d2x = fma(dx, dx, d2x);
+        d1y += dy;
+        d2y = fma(dy, dy, d2y);
+        if (rk < 4) {
+          f0x += h == 0 ? jx : 0.0;
+          f0y += h == 0 ? jy : 0.0;
+        } else {
+          f1x += h == 1 ? jx : 0.0;
+          f1y += h == 1 ? jy : 0.0;
+        }
+        r2max = fmax(r2max, x * x + y * y);
+        amax = fmax(amax, jx + jy);
+        const float wv = s.win[t];
+        zx[k] = make_float2(wv * (float)ux, -wv * (float)pux);
+        zy[b][k] = make_float2(wv * (float)uy, -wv * (float)puy);
+        // the sums are taken turn by turn (an empty constraint: the compiler
+        // otherwise keeps every turn's actions in registers to sum them later)
+        asm volatile("" : "+v"(d1x), "+v"(d2x), "+v"(d1y), "+v"(d2y), "+v"(f0x), "+v"(f0y),
+                          "+v"(f1x), "+v"(f1y), "+v"(r2max), "+v"(amax));
+      }
+      fft_stages<1>(zx, 0, s.tw);
+      fft_stages<1>(zy[b], 0, s.tw);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s.z[8 * blk + k][p] = zx[k];
     }
     __syncthreads();
+    q[2 * h] = tune_of<G, T>(s);
+#pragma unroll
+    for (int b = 0; b < kBlk; ++b)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s.z[8 * (tl + kThreads * b) + k][p] = zy[b][k];
+    __syncthreads();
+    q[2 * h + 1] = tune_of<G, T>(s);
   }
-  const float qx1 = tune_of(s, 0), qy1 = tune_of(s, 1), qx2 = tune_of(s, 2), qy2 = tune_of(s, 3);
-  // action statistics: sums, first and last quarters, then the spread
-  constexpr int kQ = kRecTurns / 4;
-  double sx = 0.0, sy = 0.0, fx0 = 0.0, fx1 = 0.0, fy0 = 0.0, fy1 = 0.0;
-  for (int t = threadIdx.x; t < kRecTurns; t += blockDim.x) {
-    sx += s.jx[t];
-    sy += s.jy[t];
-    if (t < kQ) { fx0 += s.jx[t]; fy0 += s.jy[t]; }
-    if (t >= kRecTurns - kQ) { fx1 += s.jx[t]; fy1 += s.jy[t]; }
+  double v[kStats] = {d1x, d2x, f0x, f1x, d1y, d2y, f0y, f1y, r2max, amax};
+#pragma unroll
+  for (int k = 0; k < kStats; ++k) {
+    v[k] = k < 8 ? lanes_sum<G>(v[k]) : lanes_max<G>(v[k]);
+    if ((threadIdx.x & 63) < G) s.red[threadIdx.x >> 6][k][p] = v[k];
   }
-  sx = block_sum(sx, s.red);
-  sy = block_sum(sy, s.red);
-  fx0 = block_sum(fx0, s.red);
-  fx1 = block_sum(fx1, s.red);
-  fy0 = block_sum(fy0, s.red);
-  fy1 = block_sum(fy1, s.red);
-  const double mx = sx / kRecTurns, my = sy / kRecTurns;
-  double vx = 0.0, vy = 0.0;
-  for (int t = threadIdx.x; t < kRecTurns; t += blockDim.x) {
-    vx += (s.jx[t] - mx) * (s.jx[t] - mx);
-    vy += (s.jy[t] - my) * (s.jy[t] - my);
-  }
-  vx = block_sum(vx, s.red);
-  vy = block_sum(vy, s.red);
-  rmax = block_max(rmax, s.red);
-  amax = block_max(amax, s.red);
-  if (threadIdx.x == 0) {
+  __syncthreads();
+  if (threadIdx.x < G && on) {
+#pragma unroll
+    for (int k = 0; k < kStats; ++k)
+      for (int w = 1; w < T / 64; ++w)
+        v[k] = k < 8 ? v[k] + s.red[w][k][p] : fmax(v[k], s.red[w][k][p]);
+    constexpr int kQ = kRecTurns / 4;
     const double e = 1e-6 * emit;
     auto cdiff = [](double a, double b) {
       double d = fabs(a - b);
       d = d - floor(d);
       return fmin(d, 1.0 - d);
     };
-    const double a0x = sqrt(2.0 * s.jx[0] / emit), a0y = sqrt(2.0 * s.jy[0] / emit);
+    // mean j0 + <d>, variance <d^2> - <d>^2: at least <d>^2 / 1024, since the
+    // first turn is itself <d> away, so the difference loses at most ten bits
+    auto spread = [&](double j0, double d1, double d2) {
+      const double md = d1 / kRecTurns, var = d2 / kRecTurns - md * md;
+      return sqrt(var < 0.0 ? 0.0 : var) / ((j0 + md) + e);  // (a NaN stays one)
+    };
+    const double a0x = sqrt(2.0 * jx0 / emit), a0y = sqrt(2.0 * jy0 / emit);
     const double r0 = sqrt(a0x * a0x + a0y * a0y);
-    float* o = out + (size_t)p * 16;
+    float* o = out + (size_t)i * kIn;
     o[0] = (float)a0x;
     o[1] = (float)a0y;
     o[2] = (float)r0;
     o[3] = (float)atan2(a0y, a0x);
-    o[4] = qx1;
-    o[5] = qy1;
-    o[6] = qx2;
-    o[7] = qy2;
-    o[8] = (float)log10(cdiff(qx2, qx1) + 1e-12);
-    o[9] = (float)log10(cdiff(qy2, qy1) + 1e-12);
-    o[10] = (float)((fx1 / kQ + e) / (fx0 / kQ + e) - 1.0);
-    o[11] = (float)((fy1 / kQ + e) / (fy0 / kQ + e) - 1.0);
-    o[12] = (float)(sqrt(vx / kRecTurns) / (mx + e));
-    o[13] = (float)(sqrt(vy / kRecTurns) / (my + e));
-    o[14] = (float)(rmax / r_ap);
-    o[15] = (float)(amax / (r0 * r0 + 1e-6));
+    o[4] = q[0];
+    o[5] = q[1];
+    o[6] = q[2];
+    o[7] = q[3];
+    o[8] = (float)log10(cdiff(q[2], q[0]) + 1e-12);
+    o[9] = (float)log10(cdiff(q[3], q[1]) + 1e-12);
+    o[10] = (float)((v[3] / kQ + e) / (v[2] / kQ + e) - 1.0);
+    o[11] = (float)((v[7] / kQ + e) / (v[6] / kQ + e) - 1.0);
+    o[12] = (float)spread(jx0, v[0], v[1]);
+    o[13] = (float)spread(jy0, v[4], v[5]);
+    o[14] = (float)(sqrt(v[8]) / r_ap);
+    o[15] = (float)((2.0 * v[9] / emit) / (r0 * r0 + 1e-6));
   }
 }
 
-// Column mean and 1/std of features over rows with mask != 0 (one
-// workgroup, fixed reduction order): thread t accumulates rows t, t + 256,
-// ... (each row's 16 values from one 64-byte stretch), then the
-// 33 sums are reduced pairwise across the workgroup; norm = [mean[16],
-// inv_std[16]].
-__global__ void __launch_bounds__(256) k_feature_stats(const float* __restrict__ f,
-                                                       const int32_t* __restrict__ mask,
-                                                       int64_t n, float* __restrict__ norm) {
-  __shared__ double acc[33][256];
-  double s1[16], s2[16], cnt = 0.0;
-  for (int c = 0; c < 16; ++c) s1[c] = s2[c] = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    if (mask && !mask[i]) continue;
-    const float* row = f + i * 16;
-    for (int c = 0; c < 16; ++c) {
-      const double v = row[c];
-      s1[c] += v;
-      s2[c] += v * v;
+// Column mean and 1/std of features over rows with mask != 0 (one workgroup,
+// fixed reduction order): thread t holds columns 4 (t % 4) .. + 3 of rows
+// t / 4, t / 4 + 256, ... (a wave reads 16 rows, 1 KB, at once, eight rows of a
+// thread in flight), then the sums are reduced pairwise; norm = [mean[16],
+// inv_std[16]].  What bounds it: one CU's reads (a second workgroup would
+// need memory for its sums, which this call is not given): 0.63 ms for 2^20
+// rows, 107 GB/s; 2.06 ms when a thread read whole rows one after the other.
+__global__ void __launch_bounds__(1024) k_feature_stats(const float* __restrict__ f,
+                                                        const int32_t* __restrict__ mask,
+                                                        int64_t n, float* __restrict__ norm) {
+  __shared__ double acc[9][1024];
+  const int c4 = threadIdx.x & 3;
+  double s1[4] = {}, s2[4] = {}, cnt = 0.0;
+  auto add = [&](const float (&v)[4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double d = v[c];
+      s1[c] += d;
+      s2[c] = fma(d, d, s2[c]);  // the square is exact
     }
     cnt += 1.0;
+  };
+  constexpr int kRows = 256, kAhead = 8;
+  int64_t i = threadIdx.x >> 2;
+  if (!mask) {
+    for (; i + (kAhead - 1) * kRows < n; i += kAhead * kRows) {
+      float v[kAhead][4];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[k][c] = f[(i + k * kRows) * 16 + 4 * c4 + c];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) add(v[k]);
+    }
   }
-  for (int c = 0; c < 16; ++c) {
+  for (; i < n; i += kRows) {
+    if (mask && !mask[i]) continue;
+    float v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = f[i * 16 + 4 * c4 + c];
+    add(v);
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
     acc[c][threadIdx.x] = s1[c];
-    acc[16 + c][threadIdx.x] = s2[c];
+    acc[4 + c][threadIdx.x] = s2[c];
   }
-  acc[32][threadIdx.x] = cnt;
+  acc[8][threadIdx.x] = cnt;
   __syncthreads();
-  for (int st = blockDim.x / 2; st > 0; st >>= 1) {
+  for (int st = 512; st >= 4; st >>= 1) {
     if ((int)threadIdx.x < st)
-      for (int k = 0; k < 33; ++k) acc[k][threadIdx.x] += acc[k][threadIdx.x + st];
+#pragma unroll
+      for (int k = 0; k < 9; ++k) acc[k][threadIdx.x] += acc[k][threadIdx.x + st];
     __syncthreads();
   }
   if (threadIdx.x < 16) {
     const int c = threadIdx.x;
-    const double nn = acc[32][0];
-    const double m = nn > 0 ? acc[c][0] / nn : 0.0;
-    const double var = nn > 0 ? acc[16 + c][0] / nn - m * m : 1.0;
+    const double nn = acc[8][0];
+    const double m = nn > 0 ? acc[c % 4][c / 4] / nn : 0.0;
+    const double var = nn > 0 ? acc[4 + c % 4][c / 4] / nn - m * m : 1.0;
     norm[c] = (float)m;
     norm[16 + c] = (float)(1.0 / sqrt(var > 1e-30 ? var : 1.0));
   }
@@ -821,14 +951,24 @@ hipError_t launch_features(const float* rec, int64_t n, const double twiss4[4], 
                            double r_ap, const float2* tw, const float* win, float* out,
                            hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_features, dim3((unsigned)n), dim3(256), 0, s, rec, n, twiss4[0], twiss4[1],
-                     twiss4[2], twiss4[3], emit, r_ap, tw, win, out);
+  // Eight particles in 512 threads; four in 256 while that is at most one
+  // workgroup per CU (256 CUs).  us for 500 / 2,000 / 20,000 / 100,000
+  // particles: 4 in 256 threads 24 / 33 / 208 / 928, 8 in 512 27 / 30 / 192 /
+  // 921, 16 in 512 46 / 57 / 224 / 1,007, 16 in 1,024 41 / 46 / 255 / 1,258.
+  auto launch = [&](auto kernel, int64_t g, int t) {
+    const int64_t groups = (n + g - 1) / g;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((groups + 7) / 8 * 8)), dim3(t), 0, s, rec, n,
+                       twiss4[0], twiss4[1], twiss4[2], twiss4[3], emit, r_ap, tw, win, out);
+  };
+  if (n >= (int64_t)1 << 22) launch(k_features<8, 512, uint64_t>, 8, 512);
+  else if (n > 1024) launch(k_features<8, 512, uint32_t>, 8, 512);
+  else launch(k_features<4, 256, uint32_t>, 4, 256);
   return hipGetLastError();
 }
 
 hipError_t launch_feature_stats(const float* f, const int32_t* mask, int64_t n, float* norm,
                                 hipStream_t s) {
-  hipLaunchKernelGGL(k_feature_stats, dim3(1), dim3(256), 0, s, f, mask, n, norm);
+  hipLaunchKernelGGL(k_feature_stats, dim3(1), dim3(1024), 0, s, f, mask, n, norm);
   return hipGetLastError();
 }
 
