@@ -215,13 +215,10 @@ inline bool line_long(int32_t style) { return kLineStyle[style].long_cells; }
 // (the photon emitter is an out-of-line call whose register and stack cost a
 // kernel pays across its whole element loop whether it runs or not).
 //   0: none (radiation off, or a line without radiating multipoles);
-//   1: the mean loss and Gaussian quantum excitation (modes 1 and 2, the
-//      mode read at run time);
-//   2: photon by photon (mode 3).
-constexpr int32_t kRadForms = 3;
-inline int32_t rad_form(bool line_radiates, int32_t mode) {
-  return (!line_radiates || mode == 0) ? 0 : (mode == 3 ? 2 : 1);
-}
+//   1, 2, 3: the radiation mode (mean loss, with Gaussian quantum excitation,
+//      photon by photon).
+constexpr int32_t kRadForms = 4;
+inline int32_t rad_form(bool line_radiates, int32_t mode) { return line_radiates ? mode : 0; }
 // Whether an element table holds radiating multipoles (a curvature term or
 // a radiation length).
 bool table_radiates(const std::vector<uint64_t>& tab, int32_t n_el);

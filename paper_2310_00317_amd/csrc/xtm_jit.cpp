@@ -42,6 +42,9 @@ std::mutex g_mu;
 std::map<std::string, Compiled> g_cache;  // schedule + generated source -> compiled kernel
 
 uint32_t sig_of(uint64_t h) { return (uint32_t)(h & 0xffffu); }  // kernel type | order << 8
+// added to the signature of a multipole whose parameters end in the reciprocal
+// of its radiation length (straight cells)
+constexpr uint32_t kRecip = 1u << 16;
 
 struct Decomp {
   std::vector<std::vector<uint32_t>> kinds;  // element signatures of each kind
@@ -132,8 +135,8 @@ int32_t n_words(uint32_t s) {
   switch (kt) {
     case K_DRIFT: case K_DRIFT_EXP: case K_AP_CIRC: return 1;
     case K_MULT: return 2 * ((int32_t)order + 1);
-    case K_MULT_CURV: return 2 * ((int32_t)order + 1) + 3;
-    case K_MULT_LR: return 2 * ((int32_t)order + 1) + 1;
+    case K_MULT_CURV: return 2 * ((int32_t)order + 1) + 3 + ((s & kRecip) ? 1 : 0);
+    case K_MULT_LR: return 2 * ((int32_t)order + 1) + 1 + ((s & kRecip) ? 1 : 0);
     case K_RF: return 3;
     case K_SHIFT: case K_SROT: case K_AP_ELL: return 2;
     case K_AP_RECT: return 4;
@@ -160,13 +163,18 @@ enum EmitMode {
   kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kRecord = 3, kFlag = 4, kTest = 5, kFlagScalar = 6
 };
 
-// curv_lr: every bend with a curvature term has a positive radiation length.
 std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool far_rf,
-                 EmitMode mode, bool curv_lr = false) {
+                 EmitMode mode) {
   const uint32_t kt = s & 0xffu, order = (s >> 8) & 0xffu;
   auto P = [&](int32_t m) { return "(" + arr + ")[" + std::to_string(m) + "]"; };
   const bool flag = mode == kFlag || mode == kFlagScalar;
   const std::string sc = mode == kFlagScalar ? ", true" : "";  // multipole's second parameter
+  // the radiation step of a multipole whose radiation length is word m
+  auto radiation = [&](int32_t m) {
+    return flag && (s & kRecip)
+               ? "RADF(kx, ky, " + P(m) + ", " + P(m + 1) + ", " + j + ");"
+               : "RAD(kx, ky, " + P(m) + ", " + j + ");";
+  };
   std::ostringstream c;
   switch (kt) {
     case K_DRIFT: {
@@ -206,14 +214,17 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
     case K_MULT_CURV: {
       const int32_t v = 2 * ((int32_t)order + 1);
       c << "{ double kx, ky; xtmm::multipole<" << order << sc << ">(q, " << arr
-        << ", kx, ky); xtmm::curvature<" << (curv_lr ? "true" : "false") << ">(q, " << P(v) << ", " << P(v + 1) << ", " << P(v + 2)
-        << "); RAD(kx, ky, " << P(v + 2) << ", " << j << "); }";
+        << ", kx, ky); "
+        << (flag && (s & kRecip) ? "xtmm::curvature_flag(q, " : "xtmm::curvature(q, ") << P(v)
+        << ", " << P(v + 1) << ", " << P(v + 2);
+      if (flag && (s & kRecip)) c << ", " << P(v + 3) << ", bad";
+      c << "); " << radiation(v + 2) << " }";
       break;
     }
     case K_MULT_LR: {
       const int32_t v = 2 * ((int32_t)order + 1);
       c << "{ double kx, ky; xtmm::multipole<" << order << sc << ">(q, " << arr
-        << ", kx, ky); RAD(kx, ky, " << P(v) << ", " << j << "); }";
+        << ", kx, ky); " << radiation(v) << " }";
       break;
     }
     case K_RF:
@@ -269,7 +280,7 @@ int32_t kind_words(const std::vector<uint32_t>& k) {
 // code then reads its parameters as broadcast LDS reads at compile-time
 // offsets.
 std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_form,
-                     bool scalar, bool curv_lr) {
+                     bool flagged, bool scalar) {
   int32_t maxw = 1;
   for (const auto& k : d.kinds) maxw = std::max(maxw, kind_words(k));
   // the lanes of a workgroup share one LDS slot pair, filled by all of them
@@ -285,7 +296,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   // per cell (line_deferred: the tests only record the loss code; lanes lost
   // in the cell replay it afterwards)
   const bool deferred = line_deferred(style);
-  // (line_long) or once per cell without recording which test failed: the
+  // (flagged) or once per cell without recording which test failed: the
   // cell is one straight run of arithmetic, and lanes that failed some test
   // in it, or met a drift outside the short sequences' window, go through it
   // again from its entry with each test where it belongs.
@@ -311,7 +322,6 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   // -> 8.8e11 passes/s; DA ring, 131,072: 6.3e11 -> 7.8e11; FODO ring, 1M:
   // 1.95e12 -> 2.0e12.  A lone wave waits longer for scalar loads (one every
   // 64 bytes) than for LDS: DA ring, 40,000 particles, 3.8e11 against 4.05e11.
-  const bool flagged = line_long(style) && rad_form == 0;
   // particles per lane (line_ppt): one, or two whose maps interleave
   const int32_t ppt = line_ppt(style);
   std::vector<uint32_t> sigs;  // distinct element signatures of the line
@@ -337,23 +347,29 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
                     "__constant__ int elem_sig[] = {" + es.str() + "};\n"
                     "__constant__ int elem_off[] = {" + eo.str() + "};\n";
   }
-  // a kernel with radiation steps calls its RF sine out of line
+  // a kernel with radiation steps and branches calls its RF sine out of line
   bool far_rf = false;
-  if (rad_form != 0)
+  if (rad_form != 0 && !flagged)
     for (const auto& k : d.kinds)
       for (uint32_t e : k) far_rf |= ((e & 0xffu) == K_MULT_CURV || (e & 0xffu) == K_MULT_LR);
-  // the radiation step after a radiating multipole (rad_form): none; the
-  // mean and Gaussian models with the mode read at run time; photon by photon
+  // the radiation step after a radiating multipole (rad_form): none or the
+  // mode's; RADF, in a straight cell, with its tests collected
   std::string rad_macro;
   if (rad_form == 0)
-    rad_macro = "#define RAD(kx, ky, lr, j) ((void)0)\n";
+    rad_macro = "#define RAD(kx, ky, lr, j) ((void)0)\n"
+                "#define RADF(kx, ky, lr, ilr, j) ((void)0)\n";
   else
-    rad_macro = std::string("#define RAD(kx, ky, lr, j) xtmm::radiate_at<true, ") +
-                (rad_form == 2 ? "true>(q, kx, ky, lr, 3, " : "false>(q, kx, ky, lr, r.rad_mode, ") +
-                "r.seed, pid, \\\n"
+    rad_macro = std::string("#define RAD(kx, ky, lr, j) xtmm::radiate_at<") +
+                (rad_form == 3 ? "true" : "false") + ">(q, kx, ky, lr, " +
+                std::to_string(rad_form) +
+                ", r.seed, pid, \\\n"
                 "    t0 + t, ec + (j), r.gamma0, r.c_mean, r.c_quant, r.p0c, beta0, two_over_beta0, "
                 "\\\n"
-                "    r.photon_table, r.c_nphot, r.c_ucrit)\n";
+                "    r.photon_table, r.c_nphot, r.c_ucrit)\n"
+                "#define RADF(kx, ky, lr, ilr, j) xtmm::radiate_flag<" +
+                std::to_string(rad_form) + ">(q, kx, ky, lr, ilr, rr, ip0c, \\\n    " +
+                (rad_form == 2 ? "xtmm::gauss_at(r.seed, pid, t0 + t, ec + (j), 0)" : "0.0") +
+                ", beta0, two_over_beta0, bad)\n";
   const int32_t per_thread = (maxw + lanes - 1) / lanes;
   std::ostringstream s;
   s << "#include \"xtm_maps.h\"\n"
@@ -433,6 +449,14 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "  const double beta0 = r.beta0, two_over_beta0 = r.two_over_beta0;\n"
          "  const long long pid = P.pid[pi];\n"
          "  xtmm::refresh(q, beta0);\n";
+    if (flagged && rad_form != 0)
+      s << "  // what the short radiation steps take for granted of their operands\n"
+           "  // (in vector registers: the scalar ones are taken by the series' coefficients)\n"
+           "  const xtmm::Rad rr{xtmm::in_vector(r.gamma0), xtmm::in_vector(r.c_mean),\n"
+           "                     xtmm::in_vector(r.c_quant), xtmm::in_vector(r.p0c)};\n"
+           "  const double ip0c = 1.0 / rr.p0c;\n"
+           "  const bool rad_ok = (q.rpp == 1.0 / (1.0 + q.delta)) & (r.p0c >= 0x1p-100) &\n"
+           "                      (r.p0c <= 0x1p100);\n";
   } else {
     // two particles per lane: slots i0 and i0 + LANES of the workgroup's range
     s << "  const int t0 = ctrl[1];\n"
@@ -561,7 +585,8 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "      const xtmm::Pt qc = q;\n";
   if (flagged)
     s << "      const xtmm::Pt qc = q;\n"
-         "      bool bad = !xtmm::drift_range(q);\n";
+         "      bool bad = !xtmm::drift_range(q)"
+      << (rad_form != 0 ? " | !rad_ok" : "") << ";\n";
   for (size_t k = 0; k < d.kinds.size(); ++k) {
     s << "      " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
     const auto& kd = d.kinds[k];
@@ -616,8 +641,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
       const std::string stmt =
           emit(kd[j], arr, std::to_string(j), far_rf,
                scalar ? kFlagScalar
-                      : (flagged ? kFlag : (deferred ? kMarkOnly : kSaveAtLoss)),
-               curv_lr);
+                      : (flagged ? kFlag : (deferred ? kMarkOnly : kSaveAtLoss)));
       if (stmt.empty()) continue;
       if (ppt == 1) {
         s << "        " << stmt << "\n";
@@ -960,9 +984,12 @@ Compiled compile(const std::string& src, const char* name, bool ilp_sched) {
 
 namespace {
 // Signature, parameter-word position and parameter words of each element of
-// a host element table.
+// a host element table.  curv, rad: the parameters of a bend with a curvature
+// term and of a multipole with a radiation length alone are followed by the
+// reciprocal of that length, their last word.
 void split_table(const std::vector<uint64_t>& tab, int32_t n_el, std::vector<uint32_t>* sig,
-                 std::vector<int32_t>* word_of, std::vector<double>* prm) {
+                 std::vector<int32_t>* word_of, std::vector<double>* prm, bool curv = false,
+                 bool rad = false) {
   size_t off = 0;
   for (int32_t e = 0; e < n_el; ++e) {
     const uint64_t h = tab[off];
@@ -973,6 +1000,31 @@ void split_table(const std::vector<uint64_t>& tab, int32_t n_el, std::vector<uin
       double d;
       std::memcpy(&d, &tab[off + 1 + w], 8);
       prm->push_back(d);
+    }
+    const uint32_t kt = (uint32_t)(h & 0xffu);
+    if ((curv && kt == K_MULT_CURV) || (rad && kt == K_MULT_LR)) {
+      sig->back() |= kRecip;
+      prm->push_back(1.0 / prm->back());
+    }
+    off += 1 + nw;
+  }
+}
+
+// Whether the short sequences of the curvature term serve every bend of a
+// table (curv), and those of the radiation step every radiating element (rad).
+void short_lengths(const std::vector<uint64_t>& tab, int32_t n_el, bool* curv, bool* rad) {
+  auto in_range = [](uint64_t w) {
+    double v;
+    std::memcpy(&v, &w, 8);
+    return std::fabs(v) >= 0x1p-100 && std::fabs(v) <= 0x1p100;
+  };
+  size_t off = 0;
+  for (int32_t e = 0; e < n_el; ++e) {
+    const uint32_t kt = (uint32_t)(tab[off] & 0xffu), nw = (uint32_t)((tab[off] >> 16) & 0xffffu);
+    if (kt == K_MULT_CURV || kt == K_MULT_LR) {  // the length is the last word
+      const bool ok = in_range(tab[off + nw]) && !(tab[off + nw] >> 63);
+      *rad &= ok;
+      if (kt == K_MULT_CURV) *curv &= ok && in_range(tab[off + nw - 2]);
     }
     off += 1 + nw;
   }
@@ -1045,14 +1097,21 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   std::vector<int32_t> word_of;  // parameter-array offset of each element
   std::vector<double> prm;
   sig.reserve(n_el);
-  split_table(*tabs[0], n_el, &sig, &word_of, &prm);
+  bool curv = line_long(style), rad = rad_form != 0;
+  for (const auto* t : tabs) short_lengths(*t, n_el, &curv, &rad);
+  // straight cells: no photon emitter (its loop is a branch), and the mean and
+  // Gaussian models where every radiation length suits their short sequences
+  const bool flagged = line_long(style) && (rad_form == 0 || (rad_form != 3 && curv && rad));
+  curv &= flagged;
+  rad &= flagged;
+  split_table(*tabs[0], n_el, &sig, &word_of, &prm, curv, rad);
   if (prm.empty()) prm.push_back(0.0);
   const size_t stride = prm.size();
   for (size_t v = 1; v < tabs.size(); ++v) {
     std::vector<uint32_t> sv;
     std::vector<int32_t> wv;
     std::vector<double> pv;
-    split_table(*tabs[v], n_el, &sv, &wv, &pv);
+    split_table(*tabs[v], n_el, &sv, &wv, &pv, curv, rad);
     if (pv.empty()) pv.push_back(0.0);
     if (sv != sig || pv.size() != stride) {
       k->error = "lattice variant " + std::to_string(v) + " differs in element structure";
@@ -1081,17 +1140,11 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   // variants) and the photon form (4 % slower) keep the default; the straight
   // cells take it (with the default, 200 registers instead of 141 on the FODO
   // ring and 9.4 ms instead of 8.8 ms for 1M particles)
-  const bool flagged = line_long(style) && rad_form == 0;
-  const bool ilp = flagged || (!batched && rad_form != 2);
-  // whether every curvature term has a positive radiation length (a test the
-  // straight cells then leave out)
-  bool curv_lr = flagged;
-  for (int32_t e = 0; e < n_el && curv_lr; ++e)
-    if ((sig[e] & 0xffu) == K_MULT_CURV)
-      for (size_t v = 0; v < tabs.size(); ++v)
-        curv_lr &= prm[v * stride + word_of[e] + n_words(sig[e]) - 1] > 0.0;
-  if (flagged) k->wide_source = generate(d, style, batched, rad_form, true, curv_lr);
-  return finish_kernel(d, generate(d, style, batched, rad_form, false, curv_lr), "xtm_line", ilp,
+  const bool ilp = flagged || (!batched && rad_form != 3);
+  // (no wide form with radiation, whose constants need the scalar registers:
+  // electron ring, 131,072 particles, two turns, 13.3 ms against 11.3 ms)
+  if (flagged && rad_form == 0) k->wide_source = generate(d, style, batched, rad_form, true, true);
+  return finish_kernel(d, generate(d, style, batched, rad_form, flagged, false), "xtm_line", ilp,
                        word_of, prm, k);
 }
 

@@ -107,7 +107,7 @@ __device__ __forceinline__ void multipole_n(xtmm::Pt& q, const double* __restric
 __device__ __forceinline__ void maybe_radiate(xtmm::Pt& q, double kx, double ky, double lr,
                                               const KernelRef& r, long long pid, int turn,
                                               int element) {
-  xtmm::radiate_at<true>(q, kx, ky, lr, r.rad_mode, r.seed, pid, turn, element, r.gamma0, r.c_mean,
+  xtmm::radiate_at(q, kx, ky, lr, r.rad_mode, r.seed, pid, turn, element, r.gamma0, r.c_mean,
                    r.c_quant, r.p0c, r.beta0, r.two_over_beta0, r.photon_table, r.c_nphot,
                    r.c_ucrit);
 }
