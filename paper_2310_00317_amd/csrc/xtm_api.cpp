@@ -1894,17 +1894,14 @@ bool solve_i_minus(const double A[4][4], const double b[4], double x[4]) {
 // last): the generated recording kernel, compiled on the lattice's first
 // call, or the element interpreter (k_record) for a line without a cell
 // decomposition.  Both apply the same maps, so the records are the same.
-// all_rows = false: only the row after the turn is needed (the generated
-// kernel then stores only that row; the interpreter stores every row).
 hipError_t record_turn(xtm_lattice_s* L, const double* d_in, int64_t n, double* d_out,
-                       hipStream_t s, bool all_rows = true) {
+                       hipStream_t s) {
   if (!L->rec_line.tried && L->n_el > 0) {
     L->rec_line.tried = true;
     build_record_kernel(L->fwd_h, L->n_el, &L->rec_line);
   }
   if (L->rec_line.ok)
-    return launch_line_record(L->rec_line, L->n_el, d_in, n, d_out, all_rows,
-                              kref(L->ref, 0, 0), s);
+    return launch_line_record(L->rec_line, L->n_el, d_in, n, d_out, kref(L->ref, 0, 0), s);
   return launch_record(L->fwd_d, L->fwd_seg_d, (int32_t)(L->fwd_seg_h.size() / 3), L->n_el, d_in,
                        n, d_out, kref(L->ref, 0, 0), s);
 }
@@ -1944,10 +1941,19 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
       return fail(XTM_E_NOMEM, "twiss scratch allocation");
     }
     std::vector<double> out(out_n);
-    auto run = [&](const double u[4], bool with_delta, bool all_rows) -> xtm_status {
-      const int64_t m = with_delta ? 11 : 9;
+    // one recorded turn of all the probes around u; the coordinates after it
+    // (every row costs the kernel no more than the last one, so the probes of
+    // the orbit the search ends at are the recorded turn)
+    auto fetch = [&](size_t first) -> xtm_status {
+      if (hipMemcpyAsync(out.data() + first, d_out + first, (out_n - first) * sizeof(double),
+                         hipMemcpyDeviceToHost, s) != hipSuccess ||
+          hipStreamSynchronize(s) != hipSuccess)
+        return fail(XTM_E_HIP, "twiss download");
+      return XTM_OK;
+    };
+    auto run = [&](const double u[4]) -> xtm_status {
       double c[11][6];
-      for (int64_t r = 0; r < m; ++r) {
+      for (int64_t r = 0; r < np; ++r) {
         for (int k = 0; k < 4; ++k) c[r][k] = u[k];
         c[r][4] = 0.0;
         c[r][5] = delta0;
@@ -1956,25 +1962,15 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
         c[1 + 2 * k][k] += h;
         c[2 + 2 * k][k] -= h;
       }
-      if (with_delta) {
-        c[9][5] = delta0 + hd;
-        c[10][5] = delta0 - hd;
-      }
-      if (hipMemcpyAsync(d_in, c, m * 6 * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
+      c[9][5] = delta0 + hd;
+      c[10][5] = delta0 - hd;
+      if (hipMemcpyAsync(d_in, c, sizeof c, hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(XTM_E_HIP, "twiss upload");
-      if (record_turn(L, d_in, m, d_out, s, all_rows) != hipSuccess)
+      if (record_turn(L, d_in, np, d_out, s) != hipSuccess)
         return fail(XTM_E_HIP, "twiss record launch");
-      const size_t first = all_rows ? 0 : (size_t)n_el * m * 6;
-      const size_t cnt = (all_rows ? (size_t)(n_el + 1) : 1) * m * 6;
-      if (hipMemcpyAsync(out.data() + first, d_out + first, cnt * sizeof(double),
-                         hipMemcpyDeviceToHost, s) != hipSuccess ||
-          hipStreamSynchronize(s) != hipSuccess)
-        return fail(XTM_E_HIP, "twiss download");
-      return XTM_OK;
+      return fetch((size_t)n_el * np * 6);
     };
-    auto at = [&](int64_t m, int32_t e, int r, int k) {
-      return out[((size_t)e * m + r) * 6 + k];
-    };
+    auto at = [&](int32_t e, int r, int k) { return out[((size_t)e * np + r) * 6 + k]; };
     double u[4] = {0.0, 0.0, 0.0, 0.0};
     if (co_guess)
       for (int k = 0; k < 4; ++k) u[k] = co_guess[k];
@@ -1982,15 +1978,15 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
     double res = INFINITY, best = INFINITY;
     double J[4][4];
     for (;;) {
-      st = run(u, false, false);
+      st = run(u);
       if (st != XTM_OK) break;
       double F[4];
       for (int k = 0; k < 4; ++k)
         for (int i = 0; i < 4; ++i)
-          J[i][k] = (at(9, n_el, 1 + 2 * k, i) - at(9, n_el, 2 + 2 * k, i)) / (2.0 * h);
+          J[i][k] = (at(n_el, 1 + 2 * k, i) - at(n_el, 2 + 2 * k, i)) / (2.0 * h);
       res = 0.0;
       for (int i = 0; i < 4; ++i) {
-        F[i] = at(9, n_el, 0, i) - u[i];
+        F[i] = at(n_el, 0, i) - u[i];
         res = std::max(res, std::fabs(F[i]));
       }
       if (std::isnan(F[0] + F[1] + F[2] + F[3])) res = NAN;
@@ -2004,7 +2000,7 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
       for (int k = 0; k < 4; ++k) u[k] = u[k] + du[k];
       ++it;
     }
-    if (st == XTM_OK) st = run(u, true, true);
+    if (st == XTM_OK) st = fetch(0);
     if (st == XTM_OK) {
       // per-element maps, momentum columns, dispersion and uncoupled optics
       std::vector<double> M((size_t)(n_el + 1) * 16), md((size_t)(n_el + 1) * 4);
@@ -2012,8 +2008,8 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
         for (int i = 0; i < 4; ++i) {
           for (int k = 0; k < 4; ++k)
             M[(size_t)e * 16 + i * 4 + k] =
-                (at(11, e, 1 + 2 * k, i) - at(11, e, 2 + 2 * k, i)) / (2.0 * h);
-          md[(size_t)e * 4 + i] = (at(11, e, 9, i) - at(11, e, 10, i)) / (2.0 * hd);
+                (at(e, 1 + 2 * k, i) - at(e, 2 + 2 * k, i)) / (2.0 * h);
+          md[(size_t)e * 4 + i] = (at(e, 9, i) - at(e, 10, i)) / (2.0 * hd);
         }
       double Jt[4][4], eta0[4];
       for (int i = 0; i < 4; ++i)
@@ -2045,7 +2041,7 @@ xtm_status xtm_twiss(xtm_lattice L, double delta0, double h, double hd, int32_t 
               if (de.type == XTM_DRIFT || de.type == XTM_DRIFT_EXPANDED) s_acc = s_acc + de.length;
             }
             row[0] = s_acc;
-            for (int k = 0; k < 4; ++k) row[1 + k] = at(11, e, 0, k);
+            for (int k = 0; k < 4; ++k) row[1 + k] = at(e, 0, k);
             const double* Me = &M[(size_t)e * 16];
             for (int pl = 0; pl < 2; ++pl) {
               const int o = 2 * pl;

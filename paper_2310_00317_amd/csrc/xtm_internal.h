@@ -230,12 +230,11 @@ bool build_line_kernel(const std::vector<uint64_t>& tab, int32_t n_el, int32_t s
 bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& tabs, int32_t n_el,
                              int32_t style, bool batched, int32_t rad_form, LineKernel* k);
 // The generated recording kernel of optics by tracking (the coordinates of
-// one turn at every element's entry, as launch_record, or with all_rows =
-// false only after the turn, row n_el); fails if the line has no cell
-// decomposition.
+// one turn at every element's entry, as launch_record); fails if the line has
+// no cell decomposition.
 bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKernel* k);
 hipError_t launch_line_record(const LineKernel& k, int32_t n_el, const double* c6, int64_t n,
-                              double* out, bool all_rows, KernelRef r, hipStream_t s);
+                              double* out, KernelRef r, hipStream_t s);
 void free_line_kernel(LineKernel* k);
 // Largest number of alive particles that the form staging its parameters in
 // LDS serves where a wide form exists: one wave on each of 1,024 SIMDs.

@@ -71,9 +71,8 @@ constexpr int kLongCode = 64;
 // less costs the last overlap (thick ring, 30,000: 3.48e11 at every drift,
 // 3.65e11-3.80e11 at every second to fourth)
 constexpr int32_t kSettleWords = 12;
-// the recording kernel buffers a cell's rows in LDS: at most 16 elements a
-// cell (16 x 64 lanes x 48 bytes)
-constexpr int kMaxRecordUnit = 16;
+// cells ahead of the tracking wave that the recording kernel's other wave loads
+constexpr int32_t kAhead = 4;
 
 // (Longest units first: a unit that cannot beat the best cover so far, or that
 // needs too much code, is given up at once, which leaves a few full scans of the
@@ -162,16 +161,13 @@ int32_t n_words(uint32_t s) {
 // coordinates at the element; kMarkOnly only records the loss code (the cell
 // is replayed for lanes lost in it, see generate); kReplay applies the map
 // alone (the replay itself).
-// kRecord: the maps for optics by tracking (apertures not applied; a lane
-// whose drift finds no real longitudinal momentum keeps its entry
-// coordinates and applies no further maps).
 // kFlag: no branch and no store; a failing test, or operands the drift's short
 // sequences do not serve, set `bad`.
 // kTest: the generic drift, and a loss test's result in `ok` with the state a
 // lost particle takes in `ls`.
 // kFlagScalar: as kFlag, the parameters in scalar registers.
 enum EmitMode {
-  kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kRecord = 3, kFlag = 4, kTest = 5, kFlagScalar = 6
+  kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kFlag = 4, kTest = 5, kFlagScalar = 6
 };
 
 std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool far_rf,
@@ -195,14 +191,11 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
         c << "(void)xtmm::drift_exact(q, " << P(0) << ", " << any << ");";
       else if (flag)
         c << "xtmm::drift_flag<" << (mode == kFlagScalar ? "true" : "false") << ">(q, " << P(0)
-          << ", " << any << ", bad);";
+          << ", " << any << ", a_min, bad);";
       else if (mode == kTest)
         c << "{ const xtmm::DriftIn d_ = xtmm::drift_in(q); double lp_, dq_; "
           << "xtmm::drift_generic(" << P(0) << ", d_, lp_, dq_); "
           << "xtmm::drift_apply(q, lp_, dq_); ok = d_.pz2 > 0.0; ls = -1; }";
-      else if (mode == kRecord)
-        c << "{ const xtmm::Pt q0_ = q; if (!xtmm::drift_exact(q, " << P(0) << ", " << any
-          << ")) { q = q0_; alive = false; } }";
       else if (mode == kMarkOnly)
         c << "xtmm::mark(xtmm::drift_exact(q, " << P(0) << ", " << any << "), code, st, e0 + "
           << j << ", -1);";
@@ -241,7 +234,9 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
     case K_RF:
       c << (far_rf ? "xtmm::rf_far(q, " : "xtmm::rf(q, ") << P(0) << ", " << P(1) << ", " << P(2)
         << ", beta0, two_over_beta0);";
-      if (flag) c << " bad |= !xtmm::drift_range(q);";
+      if (flag)
+        c << " bad |= !xtmm::drift_range(q); "
+             "if (__builtin_bit_cast(unsigned long long, q.u) != 0) a_min = xtmm::kDriftMin;";
       break;
     case K_SHIFT:
       c << "xtmm::xyshift(q, " << P(0) << ", " << P(1) << ");";
@@ -252,7 +247,7 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
     case K_AP_CIRC:
     case K_AP_ELL:
     case K_AP_RECT: {
-      if (mode == kReplay || mode == kRecord) break;  // a test, no change of coordinates
+      if (mode == kReplay) break;  // a test, no change of coordinates
       std::string test;
       if (kt == K_AP_CIRC) test = "xtmm::in_circle(q, " + P(0) + ")";
       else if (kt == K_AP_ELL) test = "xtmm::in_ellipse(q, " + P(0) + ", " + P(1) + ")";
@@ -284,6 +279,94 @@ int32_t kind_words(const std::vector<uint32_t>& k) {
   return w;
 }
 
+// Constant tables of a second, element by element pass through a cell: per
+// kind its first entry; per entry its element's signature (the index in
+// `sigs`, the line's distinct ones) and parameter offset.
+std::string replay_tables(const Decomp& d, std::vector<uint32_t>* sigs) {
+  std::ostringstream kf, es, eo;
+  int32_t n = 0;
+  for (const auto& k : d.kinds) {
+    kf << n << ", ";
+    int32_t o = 0;
+    for (uint32_t e : k) {
+      size_t g = 0;
+      while (g < sigs->size() && (*sigs)[g] != e) ++g;
+      if (g == sigs->size()) sigs->push_back(e);
+      es << g << ", ";
+      eo << o << ", ";
+      o += n_words(e);
+      ++n;
+    }
+  }
+  kf << n;
+  return "__constant__ int kind_first[] = {" + kf.str() + "};\n"
+         "__constant__ int elem_sig[] = {" + es.str() + "};\n"
+         "__constant__ int elem_off[] = {" + eo.str() + "};\n";
+}
+
+// For element m of a kind: the element before whose arithmetic its words are
+// read, m - 1, or, for an element of many words (a high-order multipole) after
+// a short test or frame change, m - 2: the aperture's few operations would not
+// cover the multipole's reads.  (Reading a drift's one word that early costs
+// the saturated rings more registers than it saves.)
+std::vector<size_t> reads_ahead(const std::vector<uint32_t>& kd) {
+  std::vector<size_t> before(kd.size(), 0);
+  for (size_t m = 1; m < kd.size(); ++m) {
+    const uint32_t kp = kd[m - 1] & 0xffu;
+    const bool short_prev = kp == K_AP_CIRC || kp == K_AP_ELL || kp == K_AP_RECT ||
+                            kp == K_SHIFT || kp == K_SROT || kp == K_MARKER;
+    before[m] = (short_prev && m >= 2 && n_words(kd[m]) >= 8) ? m - 2 : m - 1;
+  }
+  return before;
+}
+
+// Registers of an element's parameters (element j, first word `off`), read in
+// one group.
+void read_words(std::ostringstream& s, uint32_t sig, size_t j, int32_t off) {
+  const int32_t nw = n_words(sig);
+  if (nw == 0) return;
+  s << "        double w" << j << "[" << nw << "];\n"
+    << "#pragma unroll\n"
+    << "        for (int m = 0; m < " << nw << "; ++m) w" << j << "[m] = p[" << off << " + m];\n";
+}
+
+// The statements of one straight cell.  A drift starts from settled momenta,
+// and the reads that follow stay behind this point (both pass through an empty
+// register constraint); in between, the arithmetic may move.  at(j): a
+// statement before element j, and whether the element is left out.
+template <typename At>
+void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool scalar, At at) {
+  std::vector<int32_t> off(kd.size() + 1, 0);
+  for (size_t j = 0; j < kd.size(); ++j) off[j + 1] = off[j] + n_words(kd[j]);
+  const std::vector<size_t> before = reads_ahead(kd);
+  if (!kd.empty()) read_words(s, kd[0], 0, 0);
+  int32_t since = 0;  // parameter words since the last settled point
+  for (size_t j = 0; j < kd.size(); ++j) {
+    const uint32_t kt = kd[j] & 0xffu;
+    const bool settle = (kt == K_DRIFT || kt == K_DRIFT_EXP) && since >= kSettleWords;
+    if (settle) since = 0;
+    since += n_words(kd[j]);
+    s << "        asm volatile(\"\" : \"+" << (scalar ? "s" : "v") << "\"(p)"
+      << (settle ? ", \"+v\"(q.px), \"+v\"(q.py), \"+v\"(q.zeta)" : "") << ");\n";
+    for (size_t m = j + 1; m < kd.size() && m <= j + 2; ++m)
+      if (before[m] == j) read_words(s, kd[m], m, off[m]);
+    const std::pair<std::string, bool> extra = at(j);
+    if (!extra.first.empty()) s << "        " << extra.first << "\n";
+    if (extra.second) continue;
+    const std::string arr =
+        n_words(kd[j]) > 0 ? "w" + std::to_string(j) : "p + " + std::to_string(off[j]);
+    const std::string stmt =
+        emit(kd[j], arr, std::to_string(j), false, scalar ? kFlagScalar : kFlag);
+    if (!stmt.empty()) s << "        " << stmt << "\n";
+  }
+}
+
+// The smallest drift numerator that a lane's short sequences serve, as the
+// kernel starts; axis: the line keeps the reference particle on the axis.
+const char* a_min_init(bool axis) {
+  return axis ? "xtmm::on_axis(q) ? 0.0 : xtmm::kDriftMin" : "xtmm::kDriftMin";
+}
+
 // Generated kernel.  Per cell the workgroup holds the cell's parameters in
 // one of two LDS slots: while the waves compute cell g from slot g&1, each
 // thread has already loaded its share of cell g+1's parameters from global
@@ -291,7 +374,7 @@ int32_t kind_words(const std::vector<uint32_t>& k) {
 // code then reads its parameters as broadcast LDS reads at compile-time
 // offsets.
 std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_form,
-                     bool flagged, bool scalar) {
+                     bool flagged, bool scalar, bool axis) {
   int32_t maxw = 1;
   for (const auto& k : d.kinds) maxw = std::max(maxw, kind_words(k));
   // the lanes of a workgroup share one LDS slot pair, filled by all of them
@@ -336,28 +419,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   // particles per lane (line_ppt): one, or two whose maps interleave
   const int32_t ppt = line_ppt(style);
   std::vector<uint32_t> sigs;  // distinct element signatures of the line
-  std::string replay_tables;   // per kind: first entry; per entry: signature, offset
-  if (deferred || flagged) {
-    std::ostringstream kf, es, eo;
-    int32_t n = 0;
-    for (const auto& k : d.kinds) {
-      kf << n << ", ";
-      int32_t o = 0;
-      for (uint32_t e : k) {
-        size_t g = 0;
-        while (g < sigs.size() && sigs[g] != e) ++g;
-        if (g == sigs.size()) sigs.push_back(e);
-        es << g << ", ";
-        eo << o << ", ";
-        o += n_words(e);
-        ++n;
-      }
-    }
-    kf << n;
-    replay_tables = "__constant__ int kind_first[] = {" + kf.str() + "};\n"
-                    "__constant__ int elem_sig[] = {" + es.str() + "};\n"
-                    "__constant__ int elem_off[] = {" + eo.str() + "};\n";
-  }
+  const std::string tables = deferred || flagged ? replay_tables(d, &sigs) : std::string();
   // a kernel with radiation steps and branches calls its RF sine out of line
   bool far_rf = false;
   if (rad_form != 0 && !flagged)
@@ -405,7 +467,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
        "#define PER_THREAD " << per_thread << "\n"
        "#define LANES " << lanes << "\n"
        "#define PPT " << ppt << "\n"
-       << replay_tables <<
+       << tables <<
        "extern \"C\" __global__ void __launch_bounds__(" << lanes << ")"
     << (scalar ? " __attribute__((amdgpu_waves_per_eu(3, 4)))\n" : "\n") <<
        "xtm_line(const double* __restrict__ " << (batched ? "prm_all" : "prm")
@@ -460,6 +522,8 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "  const double beta0 = r.beta0, two_over_beta0 = r.two_over_beta0;\n"
          "  const long long pid = P.pid[pi];\n"
          "  xtmm::refresh(q, beta0);\n";
+    if (flagged)
+      s << "  double a_min = " << a_min_init(axis) << ";\n";
     if (flagged && rad_form != 0)
       s << "  // what the short radiation steps take for granted of their operands\n"
            "  // (in vector registers: the scalar ones are taken by the series' coefficients)\n"
@@ -601,58 +665,31 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   for (size_t k = 0; k < d.kinds.size(); ++k) {
     s << "      " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
     const auto& kd = d.kinds[k];
+    if (flagged) {
+      straight_cell(s, kd, scalar, [](size_t) { return std::make_pair(std::string(), false); });
+      s << "      }\n";
+      continue;
+    }
     std::vector<int32_t> off(kd.size() + 1, 0);
     for (size_t j = 0; j < kd.size(); ++j) off[j + 1] = off[j] + n_words(kd[j]);
-    // registers of element j's parameters, loaded from the slot in one group
-    auto load = [&](size_t j) {
-      const int32_t nw = n_words(kd[j]);
-      if (nw == 0) return;
-      s << "        double w" << j << "[" << nw << "];\n"
-        << "#pragma unroll\n"
-        << "        for (int m = 0; m < " << nw << "; ++m) w" << j << "[m] = p[" << off[j]
-        << " + m];\n";
-    };
-    // fetch 2: element m's words are read before element m - 1's arithmetic,
-    // or, for an element of many words (a high-order multipole) after a
-    // short test or frame change, before element m - 2's: the aperture's few
-    // operations would not cover the multipole's reads.  (Reading a drift's
-    // one word that early costs the saturated rings more registers than it
-    // saves.)
-    std::vector<size_t> read_before(kd.size(), 0);
-    for (size_t m = 1; m < kd.size(); ++m) {
-      const uint32_t kp = kd[m - 1] & 0xffu;
-      const bool short_prev = kp == K_AP_CIRC || kp == K_AP_ELL || kp == K_AP_RECT ||
-                              kp == K_SHIFT || kp == K_SROT || kp == K_MARKER;
-      read_before[m] = (short_prev && m >= 2 && n_words(kd[m]) >= 8) ? m - 2 : m - 1;
-    }
+    auto load = [&](size_t j) { read_words(s, kd[j], j, off[j]); };
+    const std::vector<size_t> read_before = reads_ahead(kd);
     if (fetch == 2 && !kd.empty()) load(0);
-    int32_t since = 0;  // parameter words since the last settled point
     for (size_t j = 0; j < kd.size(); ++j) {
       std::string arr = "p + " + std::to_string(off[j]);
       if (fetch == 1) {
         load(j);
         s << "        __builtin_amdgcn_sched_barrier(0);\n";
       } else if (fetch == 2) {
-        if (flagged) {
-          // a drift starts from settled momenta, and the reads that follow
-          // stay behind this point (both pass through an empty register
-          // constraint); in between, the arithmetic may move
-          const uint32_t kt = kd[j] & 0xffu;
-          const bool settle = (kt == K_DRIFT || kt == K_DRIFT_EXP) && since >= kSettleWords;
-          if (settle) since = 0;
-          since += n_words(kd[j]);
-          s << "        asm volatile(\"\" : \"+" << (scalar ? "s" : "v") << "\"(p)"
-            << (settle ? ", \"+v\"(q.px), \"+v\"(q.py), \"+v\"(q.zeta)" : "") << ");\n";
-        }
+        // fetch 2: the words of the elements to read ahead of this one
         for (size_t m = j + 1; m < kd.size() && m <= j + 2; ++m)
           if (read_before[m] == j) load(m);
-        if (!flagged) s << "        __builtin_amdgcn_sched_barrier(0);\n";
+        s << "        __builtin_amdgcn_sched_barrier(0);\n";
       }
       if (fetch != 0 && n_words(kd[j]) > 0) arr = "w" + std::to_string(j);
       const std::string stmt =
           emit(kd[j], arr, std::to_string(j), far_rf,
-               scalar ? kFlagScalar
-                      : (flagged ? kFlag : (deferred ? kMarkOnly : kSaveAtLoss)));
+               deferred ? kMarkOnly : kSaveAtLoss);
       if (stmt.empty()) continue;
       if (ppt == 1) {
         s << "        " << stmt << "\n";
@@ -767,22 +804,25 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
 
 // Generated recording kernel for optics by tracking: one turn of a few
 // particles from their (x, px, y, py, zeta, delta), the coordinates stored at
-// the entry of every element and after the last.  The cell structure,
-// parameter staging (two LDS slots, the next cell's words loaded during the
-// current cell) and element code are those of the tracking kernel's
-// one-wave form with the next element's parameters read ahead; apertures are
-// not applied, and a lane whose drift finds no real longitudinal momentum
-// keeps its entry coordinates and applies no further maps.  The rows of a
-// cell go to an LDS buffer and leave for global memory together at the
-// cell's end, as contiguous runs written by all lanes.
-std::string generate_record(const Decomp& d) {
-  int32_t maxw = 1, maxk = 1;
-  for (const auto& k : d.kinds) {
-    maxw = std::max(maxw, kind_words(k));
-    maxk = std::max(maxk, (int32_t)k.size());
-  }
+// the entry of every element and after the last.  Apertures are not applied,
+// and a lane whose drift finds no real longitudinal momentum keeps its entry
+// coordinates and applies no further maps.
+//   What bounds it: one wave's chain of dependent operations through the line.
+// So the wave that tracks does nothing else: cells are straight as in the
+// tracking kernel (see generate), a lane that failed a test going through its
+// cell again, rows leave as each element is entered, and the cell's parameters
+// are brought to LDS by a second wave, kAhead cells ahead (a lone lattice's
+// words come from beyond the L2).  Optics of the 20,000-element DA ring, a
+// probe turn of 11 particles with every row: 2.4 ms; 5.1 ms when the tracking
+// wave also staged parameters and moved each cell's rows through LDS, with a
+// branch per drift.
+std::string generate_record(const Decomp& d, bool axis) {
+  int32_t maxw = 1;
+  for (const auto& k : d.kinds) maxw = std::max(maxw, kind_words(k));
   constexpr int32_t lanes = 64;
   const int32_t per_thread = (maxw + lanes - 1) / lanes;
+  std::vector<uint32_t> sigs;
+  const std::string tables = replay_tables(d, &sigs);
   std::ostringstream s;
   s << "#include \"xtm_maps.h\"\n"
        "struct KRef { double beta0, two_over_beta0, gamma0, c_mean, c_quant, p0c;\n"
@@ -790,27 +830,67 @@ std::string generate_record(const Decomp& d) {
        "              float* rec; int rec_turns; int rec_n;\n"
        "              const double* photon_table; double c_nphot, c_ucrit; };\n"
        "#define RAD(kx, ky, lr, j) ((void)0)\n"
+       "#define RADF(kx, ky, lr, ilr, j) ((void)0)\n"
+       "typedef const __attribute__((address_space(3))) double* lds_double;\n"
        "#define MAXW " << maxw << "\n"
-       "#define MAXK " << maxk << "\n"
        "#define PER_THREAD " << per_thread << "\n"
        "#define LANES " << lanes << "\n"
-       "// row j of the cell in the LDS buffer (every lane writes its own)\n"
-       "#define REC(j) do { if (ALL) { double2* r_ = rows + ((j) * LANES + lane) * 3; \\\n"
-       "    r_[0] = make_double2(q.x, q.px); r_[1] = make_double2(q.y, q.py); \\\n"
-       "    r_[2] = make_double2(q.zeta, q.delta); } } while (0)\n"
-       "// ALL: every row, else only the row after the turn (one kernel for both,\n"
-       "// each body specialised)\n"
-       "template <bool ALL>\n"
-       "__device__ __forceinline__ void record_body(const double* __restrict__ prm,\n"
-       "    const int* __restrict__ cells, int n_cells, int n_el, const double* __restrict__ c6,\n"
-       "    long long n, double* __restrict__ out, const KRef& r, double* slot, double2* rows) {\n"
-       "  const int lane = threadIdx.x;\n"
-       "  const long long i0 = (long long)blockIdx.x * LANES;\n"
-       "  const long long i = i0 + lane;\n"
+       "#define AHEAD " << kAhead << "\n"
+    << tables <<
+       "// the lane's row of the element entered, and on to the next element's\n"
+       "#define ROW(to) do { (to)[0] = make_double2(q.x, q.px); \\\n"
+       "    (to)[1] = make_double2(q.y, q.py); (to)[2] = make_double2(q.zeta, q.delta); \\\n"
+       "    (to) += row; } while (0)\n"
+       "// (LDS only: the rows on their way to memory are not waited for)\n"
+       "#define BARRIER() do { __builtin_amdgcn_s_waitcnt(0xc07f); \\\n"
+       "    asm volatile(\"\" ::: \"memory\"); __builtin_amdgcn_s_barrier(); \\\n"
+       "    asm volatile(\"\" ::: \"memory\"); } while (0)\n"
+       "extern \"C\" __global__ void __launch_bounds__(2 * LANES)\n"
+       "// (prm without __restrict__: its loads then stay before the barriers they are\n"
+       "// written before, instead of sinking to their use)\n"
+       "xtm_record(const double* prm, const int* __restrict__ cells, int n_cells,\n"
+       "           int n_el, const double* __restrict__ c6, long long n,\n"
+       "           double* __restrict__ out, KRef r) {\n"
+       "  __shared__ double slot[2 * MAXW];\n"
+       "  const int lane = threadIdx.x & (LANES - 1);\n"
+       "  // (constant address space: scalar loads on either side of the barriers)\n"
+       "  typedef int cell __attribute__((ext_vector_type(4)));\n"
+       "  const __attribute__((address_space(4))) cell* cells4 =\n"
+       "      (const __attribute__((address_space(4))) cell*)(unsigned long long)cells;\n"
+       "  if (__builtin_amdgcn_readfirstlane(threadIdx.x) >= LANES) {\n"
+       "    // cell c's words lie in slot c % 2 from the barrier before it; set\n"
+       "    // k % AHEAD of registers holds those of cell k on their way.  Every lane\n"
+       "    // loads (past the cell's words its first, past the line its last cell; the\n"
+       "    // parameter array ends in a pad word), so no load is under a branch.\n"
+       "    double pre[AHEAD][PER_THREAD];\n"
+       "    auto load = [&](int k, int c) {\n"
+       "      const cell rc = cells4[c < n_cells ? c : n_cells - 1];\n"
+       "#pragma unroll\n"
+       "      for (int m = 0; m < PER_THREAD; ++m) {\n"
+       "        const int w = lane + m * LANES;\n"
+       "        pre[k][m] = prm[rc.y + (w < rc.w ? w : 0)];\n"
+       "      }\n"
+       "    };\n"
+       "#pragma unroll\n"
+       "    for (int k = 0; k < AHEAD; ++k) load(k, k);\n"
+       "    for (int c = 0; c <= n_cells; c += AHEAD) {\n"
+       "#pragma unroll\n"
+       "      for (int k = 0; k < AHEAD; ++k) {\n"
+       "        if (c + k > n_cells) break;\n"
+       "        // cell c + k into its slot while the other wave tracks cell c + k - 1\n"
+       "#pragma unroll\n"
+       "        for (int m = 0; m < PER_THREAD; ++m) {\n"
+       "          const int w = lane + m * LANES;\n"
+       "          if (w < MAXW) slot[((c + k) & 1) * MAXW + w] = pre[k][m];\n"
+       "        }\n"
+       "        load(k, c + k + AHEAD);\n"
+       "        BARRIER();\n"
+       "      }\n"
+       "    }\n"
+       "    return;\n"
+       "  }\n"
+       "  const long long i = (long long)blockIdx.x * LANES + lane;\n"
        "  const bool act = i < n;\n"
-       "  // the block's particles: its rows of one element are nb_ consecutive 48-byte rows\n"
-       "  const int nb_ = (int)(n - i0 < LANES ? n - i0 : LANES);\n"
-       "  double2* __restrict__ out2 = reinterpret_cast<double2*>(out);\n"
        "  const double beta0 = r.beta0, two_over_beta0 = r.two_over_beta0;\n"
        "  (void)two_over_beta0;\n"
        "  xtmm::Pt q{};\n"
@@ -824,121 +904,62 @@ std::string generate_record(const Decomp& d) {
        "    q.rvv = (1.0 + dl) / (1.0 + beta0 * q.ptau);\n"
        "    xtmm::refresh(q, beta0);\n"
        "  }\n"
+       "  double a_min = " << a_min_init(axis) << ";\n"
+       "  const unsigned long long row = 3ull * n;\n"
+       "  double2* __restrict__ to = reinterpret_cast<double2*>(out) + 3 * i;\n"
        "  bool alive = act;\n"
-       "  // the coordinates have arrived before the cell loop: otherwise the\n"
-       "  // loop's first uses of them would carry a wait for every load in\n"
-       "  // flight, the next cell's parameters included, on every cell\n"
-       "  __builtin_amdgcn_s_waitcnt(0);\n"
-       "  {\n"
-       "    const int off0 = cells[1], nw0 = cells[3];\n"
-       "    for (int w = lane; w < nw0; w += LANES) slot[w] = prm[off0 + w];\n"
-       "  }\n"
-       "  // parameters two cells ahead: the words of cell c + 1 arrived during\n"
-       "  // cell c - 1 (a lone wave reads each cell's words once, from beyond the\n"
-       "  // L2, and one cell of work does not cover that latency).  Two register\n"
-       "  // sets take turns, the loop body holding two cells, so no set is copied\n"
-       "  // (a copy would wait for the loads in flight).\n"
-       "  double preA[PER_THREAD], preB[PER_THREAD];\n"
-       "  {\n"
-       "    const int c1 = n_cells > 1 ? 1 : 0;\n"
-       "    const int off1 = cells[4 * c1 + 1], nw1 = cells[4 * c1 + 3];\n"
-       "#pragma unroll\n"
-       "    for (int k = 0; k < PER_THREAD; ++k) {\n"
-       "      const int w = lane + k * LANES;\n"
-       "      preA[k] = (w < nw1) ? prm[off1 + w] : 0.0;\n"
+       "  cell rc = cells4[0];\n"
+       "  BARRIER();\n"
+       "  for (int c = 0; c < n_cells; ++c) {\n"
+       "    const cell rn = cells4[c + 1 < n_cells ? c + 1 : c];\n"
+       "    const int kind = rc.x;\n"
+       "    double2* from = to;\n"
+       "    lds_double p = (lds_double)slot + (c & 1) * MAXW;\n"
+       "    asm volatile(\"\" : \"+v\"(p));\n"
+       "    const xtmm::Pt qc = q;\n"
+       "    // a lane that keeps its coordinates takes the second pass alone\n"
+       "    bool bad = !xtmm::drift_range(q) | !alive;\n"
+       "    if (act) {\n";
+  for (size_t k = 0; k < d.kinds.size(); ++k) {
+    s << "    " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
+    straight_cell(s, d.kinds[k], false, [&](size_t j) {
+      const uint32_t kt = d.kinds[k][j] & 0xffu;
+      return std::make_pair(std::string("ROW(to);"), kt == K_AP_CIRC || kt == K_AP_ELL || kt == K_AP_RECT);
+    });
+    s << "    }\n";
+  }
+  s << "    }\n"
+       "    bad |= !(q.x == q.x);\n"
+       "    bad &= act;\n"
+       "    if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {\n"
+       "      if (bad) {\n"
+       "        q = qc;\n"
+       "        double2* ta = from;\n"
+       "        for (int j = kind_first[kind]; j < kind_first[kind + 1]; ++j) {\n"
+       "          const double* pe = (const double*)(p + elem_off[j]);\n"
+       "          ROW(ta);\n"
+       "          if (!alive) continue;\n"
+       "          const xtmm::Pt q0 = q;\n"
+       "          bool ok = true;\n"
+       "          int ls = 0;\n"
+       "          switch (elem_sig[j]) {\n";
+  for (size_t g = 0; g < sigs.size(); ++g) {
+    const uint32_t kt = sigs[g] & 0xffu;
+    if (kt == K_AP_CIRC || kt == K_AP_ELL || kt == K_AP_RECT) continue;
+    const std::string stmt = emit(sigs[g], "pe", "0", false, kTest);
+    if (!stmt.empty()) s << "            case " << g << ": " << stmt << " break;\n";
+  }
+  s << "            default: break;\n"
+       "          }\n"
+       "          (void)ls;\n"
+       "          if (!ok) { q = q0; alive = false; }\n"
+       "        }\n"
+       "      }\n"
        "    }\n"
+       "    rc = rn;\n"
+       "    BARRIER();\n"
        "  }\n"
-       "  __syncthreads();\n"
-       "  int b = 0;\n"
-       "  for (int c = 0; c < n_cells; c += 2) {\n";
-  // one cell cc = c + half: its words in slot b, the next cell's in `cur`,
-  // the cell after that loaded into `nxt`
-  auto cell = [&](int half, const char* cur, const char* nxt) {
-    s << "  {\n"
-         "    const int cc = c + " << half << ";\n"
-         "    const int cn = (cc + 1 == n_cells) ? cc : cc + 1;\n"
-         "    const int nwn = cells[4 * cn + 3];\n"
-         "    const int c2 = (cc + 2 < n_cells) ? cc + 2 : n_cells - 1;\n"
-         "    const int off2 = cells[4 * c2 + 1], nw2 = cells[4 * c2 + 3];\n"
-         "    // every lane loads (a lane past the cell's words reads its first\n"
-         "    // word, the parameter array ends in a pad word), so the loads are\n"
-         "    // not under a branch and the waits for them can count\n"
-         "#pragma unroll\n"
-         "    for (int k = 0; k < PER_THREAD; ++k) {\n"
-         "      const int w = lane + k * LANES;\n"
-         "      const double v_ = prm[off2 + (w < nw2 ? w : 0)];\n"
-         "      " << nxt << "[k] = (w < nw2) ? v_ : 0.0;\n"
-         "    }\n"
-         "    const int kind = cells[4 * cc];\n"
-         "    const int ec = cells[4 * cc + 2];\n"
-         "    const int len = (cc + 1 == n_cells ? n_el : cells[4 * (cc + 1) + 2]) - ec;\n"
-         "    int base;\n"
-         "    asm volatile(\"v_mov_b32 %0, %1\" : \"=v\"(base) : \"s\"(b * MAXW));\n"
-         "    const double* p = &slot[base & 0x3fff];\n";
-    for (size_t k = 0; k < d.kinds.size(); ++k) {
-      s << "    " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
-      const auto& kd = d.kinds[k];
-      std::vector<int32_t> off(kd.size() + 1, 0);
-      for (size_t j = 0; j < kd.size(); ++j) off[j + 1] = off[j] + n_words(kd[j]);
-      auto load = [&](size_t j) {
-        const int32_t nw = n_words(kd[j]);
-        if (nw == 0) return;
-        s << "      double w" << j << "[" << nw << "];\n"
-          << "#pragma unroll\n"
-          << "      for (int m = 0; m < " << nw << "; ++m) w" << j << "[m] = p[" << off[j]
-          << " + m];\n";
-      };
-      if (!kd.empty()) load(0);
-      for (size_t j = 0; j < kd.size(); ++j) {
-        if (j + 1 < kd.size()) load(j + 1);
-        s << "      __builtin_amdgcn_sched_barrier(0);\n";
-        const std::string arr =
-            n_words(kd[j]) > 0 ? "w" + std::to_string(j) : "p + " + std::to_string(off[j]);
-        s << "      REC(" << j << ");\n";
-        const std::string stmt = emit(kd[j], arr, std::to_string(j), false, kRecord);
-        if (!stmt.empty()) s << "      if (alive) { " << stmt << " }\n";
-      }
-      s << "    }\n";
-    }
-    s << "#pragma unroll\n"
-         "    for (int k = 0; k < PER_THREAD; ++k) {\n"
-         "      const int w = lane + k * LANES;\n"
-         "      if (w < nwn) slot[(b ^ 1) * MAXW + w] = " << cur << "[k];\n"
-         "    }\n"
-         "    b ^= 1;\n"
-         "    __syncthreads();\n"
-         "    if (ALL) {\n"
-         "      // the cell's rows, element-major: len runs of nb_ rows of three\n"
-         "      // 16-byte words, each run contiguous in the output\n"
-         "      const int per = nb_ * 3;\n"
-         "      for (int t = lane; t < len * per; t += LANES) {\n"
-         "        const int er = t / per, rem = t - er * per;\n"
-         "        const int pp = rem / 3, kk = rem - pp * 3;\n"
-         "        out2[((unsigned long long)(ec + er) * n + i0 + pp) * 3 + kk] =\n"
-         "            rows[(er * LANES + pp) * 3 + kk];\n"
-         "      }\n"
-         "      __syncthreads();\n"
-         "    }\n"
-         "  }\n";
-  };
-  cell(0, "preA", "preB");
-  s << "  if (c + 1 < n_cells)\n";
-  cell(1, "preB", "preA");
-  s << "  }\n"
-       "  if (act) {\n"
-       "    double2* o_ = out2 + ((unsigned long long)n_el * n + i) * 3;\n"
-       "    o_[0] = make_double2(q.x, q.px); o_[1] = make_double2(q.y, q.py);\n"
-       "    o_[2] = make_double2(q.zeta, q.delta);\n"
-       "  }\n"
-       "}\n"
-       "extern \"C\" __global__ void __launch_bounds__(64)\n"
-       "xtm_record(const double* __restrict__ prm, const int* __restrict__ cells, int n_cells,\n"
-       "           int n_el, const double* __restrict__ c6, long long n,\n"
-       "           double* __restrict__ out, int all_rows, KRef r) {\n"
-       "  __shared__ double slot[2 * MAXW];\n"
-       "  __shared__ double2 rows[MAXK * LANES * 3];\n"
-       "  if (all_rows) record_body<true>(prm, cells, n_cells, n_el, c6, n, out, r, slot, rows);\n"
-       "  else record_body<false>(prm, cells, n_cells, n_el, c6, n, out, r, slot, rows);\n"
+       "  if (act) ROW(to);\n"
        "}\n";
   return s.str();
 }
@@ -1042,6 +1063,29 @@ void short_lengths(const std::vector<uint64_t>& tab, int32_t n_el, bool* curv, b
 }
 }  // namespace
 
+// Whether a line without radiation keeps a particle on the axis with the
+// reference momentum there until its momentum changes: no shift, no dipole kick
+// but one that the curvature takes back (knl0 = hxl).
+static bool keeps_axis(const std::vector<uint64_t>& tab, int32_t n_el) {
+  auto word = [&](size_t at) {
+    double v;
+    std::memcpy(&v, &tab[at], 8);
+    return v;
+  };
+  size_t off = 0;
+  for (int32_t e = 0; e < n_el; ++e) {
+    const uint32_t kt = (uint32_t)(tab[off] & 0xffu), order = (uint32_t)((tab[off] >> 8) & 0xffu);
+    const size_t c0 = off + 1 + 2 * order;  // the dipole term's words
+    if (kt == K_SHIFT && (word(off + 1) != 0.0 || word(off + 2) != 0.0)) return false;
+    if (kt == K_MULT || kt == K_MULT_LR || kt == K_MULT_CURV) {
+      const double back = kt == K_MULT_CURV ? word(c0 + 2) : 0.0;
+      if (word(c0) != back || word(c0 + 1) != 0.0) return false;
+    }
+    off += 1 + (size_t)((tab[off] >> 16) & 0xffffu);
+  }
+  return true;
+}
+
 bool table_radiates(const std::vector<uint64_t>& tab, int32_t n_el) {
   size_t off = 0;
   for (int32_t e = 0; e < n_el && off < tab.size(); ++e) {
@@ -1115,6 +1159,8 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   const bool flagged = line_long(style) && (rad_form == 0 || (rad_form != 3 && curv && rad));
   curv &= flagged;
   rad &= flagged;
+  bool axis = flagged && rad_form == 0;
+  for (size_t v = 0; v < tabs.size() && axis; ++v) axis = keeps_axis(*tabs[v], n_el);
   split_table(*tabs[0], n_el, &sig, &word_of, &prm, curv, rad);
   if (prm.empty()) prm.push_back(0.0);
   const size_t stride = prm.size();
@@ -1154,8 +1200,8 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   const bool ilp = flagged || (!batched && rad_form != 3);
   // (no wide form with radiation, whose constants need the scalar registers:
   // electron ring, 131,072 particles, two turns, 13.3 ms against 11.3 ms)
-  if (flagged && rad_form == 0) k->wide_source = generate(d, style, batched, rad_form, true, true);
-  return finish_kernel(d, generate(d, style, batched, rad_form, flagged, false), "xtm_line", ilp,
+  if (flagged && rad_form == 0) k->wide_source = generate(d, style, batched, 0, true, true, axis);
+  return finish_kernel(d, generate(d, style, batched, rad_form, flagged, false, axis), "xtm_line", ilp,
                        word_of, prm, k);
 }
 
@@ -1170,16 +1216,18 @@ bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKer
   std::vector<uint32_t> sig;
   std::vector<int32_t> word_of;
   std::vector<double> prm;
-  split_table(tab, n_el, &sig, &word_of, &prm);
+  bool curv = true, rad = false;
+  short_lengths(tab, n_el, &curv, &rad);
+  split_table(tab, n_el, &sig, &word_of, &prm, curv);
   prm.push_back(0.0);  // pad word: the first word of a cell without words
   Decomp d;
-  if (!decompose(sig, &d, kMaxRecordUnit)) {
+  if (!decompose(sig, &d, kLongUnit, kLongCode)) {
     k->error = "no cell decomposition within the code budget";
     return false;
   }
-  k->style = 5;  // one-wave workgroups, the next element's parameters read ahead
+  k->style = 5;
   k->stride = (int64_t)prm.size();
-  return finish_kernel(d, generate_record(d), "xtm_record", true, word_of, prm, k);
+  return finish_kernel(d, generate_record(d, keeps_axis(tab, n_el)), "xtm_record", true, word_of, prm, k);
 }
 
 void free_line_kernel(LineKernel* k) {
@@ -1229,17 +1277,16 @@ hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* 
 }
 
 hipError_t launch_line_record(const LineKernel& k, int32_t n_el, const double* c6, int64_t n,
-                              double* out, bool all_rows, KernelRef r, hipStream_t s) {
+                              double* out, KernelRef r, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const double* prm = k.prm_d;
   const int32_t* cells = k.cells_d;
   int32_t n_cells = k.n_cells;
   long long nn = (long long)n;
-  int32_t all = all_rows ? 1 : 0;
   void* args[] = {(void*)&prm, (void*)&cells, (void*)&n_cells, (void*)&n_el, (void*)&c6,
-                  (void*)&nn,  (void*)&out,   (void*)&all,     (void*)&r};
+                  (void*)&nn,  (void*)&out,   (void*)&r};
   const unsigned grid = (unsigned)((n + 63) / 64);
-  return hipModuleLaunchKernel(k.fn, grid, 1, 1, 64, 1, 1, 0, s, args, nullptr);
+  return hipModuleLaunchKernel(k.fn, grid, 1, 1, 128, 1, 1, 0, s, args, nullptr);
 }
 
 hipError_t launch_line_batched(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,

@@ -217,8 +217,12 @@ __device__ __forceinline__ bool drift_range(const Pt& q) {
   return (q.opd2 > 0x1p-100) & (q.opd2 < 4.0);
 }
 
+// a_min: the smallest numerator served (kDriftMin; 0 for a particle known to
+// stay on the axis with the reference momentum, see on_axis).
+constexpr double kDriftMin = 0x1p-600;
 template <bool kScalar>
-__device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, bool& bad) {
+__device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, double a_min,
+                                           bool& bad) {
   const DriftIn d = drift_in(q);
   double lp, dq;
   if (len_class == 2) {
@@ -230,11 +234,21 @@ __device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, bool&
     const double b1 = 1.0 + pz;
     lp = div_by_root<kScalar>(L, pz, h);
     dq = div_in(d.a, b1);
-    bad |= !(fabs(d.a) >= 0x1p-600);
+    bad |= !(fabs(d.a) >= a_min);
     bad |= b1 == 0x1.fffffffffffffp+0;
     if (len_class == 1) bad |= all_ones_significand(pz);
   }
   drift_apply(q, lp, dq);
+}
+
+// Whether the particle is on the axis with the reference momentum.  In a line
+// that keeps such a particle there until delta changes, every drift's numerator
+// is +0, for which the short sequence gives the rounded quotient, +0, as well
+// (a numerator of -0, of delta = -0, would lose its sign).  Without this the
+// reference particle would take every cell twice.
+__device__ __forceinline__ bool on_axis(const Pt& q) {
+  return (q.x == 0.0) & (q.px == 0.0) & (q.y == 0.0) & (q.py == 0.0) &
+         (__builtin_bit_cast(unsigned long long, q.u) == 0);
 }
 
 // The exact drift's loss test alone.
