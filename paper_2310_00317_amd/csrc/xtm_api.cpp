@@ -147,9 +147,11 @@ struct xtm_particles_s {
   int32_t* idx[2] = {nullptr, nullptr};
   int32_t* lost = nullptr;  // particles lost during the last chunk
   int32_t cur = 0;          // which idx buffer holds the alive list
-  int32_t* ctrl = nullptr;  // [0] alive count, [2] count scanned by the last epilogue
+  // [0] alive count, [1] turn, [2] count scanned by the last epilogue, [3] lost
+  // count, [4] turn its chunk started from, [6, 7] the pass count (one read for all)
+  int32_t* ctrl = nullptr;
   int32_t* blockcnt = nullptr;
-  int64_t* passes = nullptr;
+  int64_t* passes = nullptr;  // in ctrl
   int64_t alive_upper = 0;  // host-side upper bound of the alive count
 };
 
@@ -326,11 +328,11 @@ KernelRef kref(const RefQ& r, int32_t rad_mode = 0, uint64_t seed = 0) {
 }
 
 xtm_status read_alive(xtm_particles_s* p, hipStream_t s, int64_t* alive, int64_t* passes) {
-  int32_t c[4];
+  int32_t c[kCtrlWords];
   HIP_TRY(hipMemcpyAsync(c, p->ctrl, sizeof c, hipMemcpyDeviceToHost, s), "read counters");
-  int64_t np = 0;
-  HIP_TRY(hipMemcpyAsync(&np, p->passes, sizeof np, hipMemcpyDeviceToHost, s), "read passes");
   HIP_TRY(hipStreamSynchronize(s), "synchronise");
+  int64_t np;
+  std::memcpy(&np, c + kCtrlPasses, sizeof np);
   if (alive) *alive = c[0];
   if (passes) *passes = np;
   p->alive_upper = c[0];
@@ -369,6 +371,7 @@ struct ChunkPlan {
   int32_t n_turns, chunk, block, variant;
   int32_t compact_every;  // compact the alive list after every this many chunks (and the last)
   bool backward, compact;
+  bool fresh;  // the pass count starts at zero
   bool ramp;  // chunk lengths 1, 2, 4, ... up to `chunk` (automatic chunking)
 };
 
@@ -444,9 +447,12 @@ hipError_t enqueue_chunks(xtm_lattice_s* L, xtm_particles_s* P, const ChunkPlan&
     ++*launches;
     // the interpreter keeps losses in registers and replays them; the
     // per-line kernels store a lost particle's coordinates as it is lost
+    // (which reads the chunk's first turn, so the turn is moved on after it)
     const bool replay = (c.variant == 4);
+    const int32_t dk = c.backward ? -k : k;
     e = launch_epilogue(in, out, replay ? P->lost : nullptr, P->alive_upper, soa, P->ctrl,
-                        P->blockcnt, P->passes, L->n_el, k, c.backward ? 1 : 0, s);
+                        P->blockcnt, P->passes, L->n_el, k, c.backward ? 1 : 0, replay ? 0 : dk,
+                        c.fresh && j == 0, s);
     if (e != hipSuccess) return e;
     if (replay && c.batch) {
       e = launch_replay_batched(c.batch->tabs_d, c.batch->first_d, (int32_t)c.batch->lats.size(),
@@ -458,7 +464,7 @@ hipError_t enqueue_chunks(xtm_lattice_s* L, xtm_particles_s* P, const ChunkPlan&
                         kr, s);
       if (e != hipSuccess) return e;
     }
-    e = launch_advance(P->ctrl, c.backward ? -k : k, s);
+    if (replay) e = launch_advance(P->ctrl, dk, s);
     if (e != hipSuccess) return e;
     if (compact_now) cur = 1 - cur;
   }
@@ -600,7 +606,10 @@ xtm_status run_turns(xtm_lattice_s* L, xtm_particles_s* P, int32_t n_turns,
   c.tab = backward ? L->bwd_d : L->fwd_d;
   const bool graph = o && o->use_graph;
   const int64_t alive_before = P->alive_upper;
-  if (stats) HIP_TRY(launch_fill_i64(P->passes, 0, s), "clear passes");
+  // the first chunk's epilogue clears the pass count; a captured sequence, which
+  // runs with and without stats, does not
+  c.fresh = stats && !graph && n_turns > 0 && P->alive_upper > 0;
+  if (stats && !c.fresh) HIP_TRY(launch_fill_i64(P->passes, 0, s), "clear passes");
   const bool timing = stats && o && o->time_kernels;
   std::vector<hipEvent_t> ev;
   int32_t launches = 0;
@@ -827,13 +836,12 @@ xtm_status xtm_particles_bind(const xtm_arrays* a, const xtm_reference* ref, xtm
     bool ok = hipMalloc(&P->idx[0], m * sizeof(int32_t)) == hipSuccess &&
               hipMalloc(&P->idx[1], m * sizeof(int32_t)) == hipSuccess &&
               hipMalloc(&P->lost, m * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&P->ctrl, 4 * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&P->blockcnt, 2 * nb * sizeof(int32_t)) == hipSuccess &&
-              hipMalloc(&P->passes, sizeof(int64_t)) == hipSuccess;
+              hipMalloc(&P->ctrl, kCtrlWords * sizeof(int32_t)) == hipSuccess &&
+              hipMalloc(&P->blockcnt, 2 * nb * sizeof(int32_t)) == hipSuccess;
+    P->passes = reinterpret_cast<int64_t*>(P->ctrl + kCtrlPasses);
     if (!ok) {
       hipFree(P->idx[0]); hipFree(P->idx[1]); hipFree(P->lost); hipFree(P->ctrl);
       hipFree(P->blockcnt);
-      hipFree(P->passes);
       delete P;
       return fail(XTM_E_NOMEM, "device allocation of particle work buffers failed");
     }
@@ -851,7 +859,6 @@ xtm_status xtm_particles_release(xtm_particles P) {
   hipFree(P->lost);
   hipFree(P->ctrl);
   hipFree(P->blockcnt);
-  hipFree(P->passes);
   delete P;
   return XTM_OK;
 }
@@ -872,9 +879,8 @@ xtm_status xtm_particles_init(xtm_particles P, const double* coords, int64_t fir
       if (e != hipSuccess) { hipFree(tmp); return hip_fail(e, "upload of coordinates"); }
       dc = tmp;
     }
-    hipError_t e = launch_init(dc, P->n, first_id, soa_of(P), kref(P->ref), s);
-    if (e == hipSuccess) e = launch_iota(P->idx[0], P->n, P->ctrl, (int32_t)P->n, 0, s);
-    if (e == hipSuccess) e = launch_fill_i64(P->passes, 0, s);
+    hipError_t e = launch_init(dc, P->n, first_id, soa_of(P), kref(P->ref), P->idx[0], P->ctrl,
+                               P->passes, s);
     if (tmp) {
       hipError_t e2 = hipStreamSynchronize(s);
       hipFree(tmp);
@@ -897,7 +903,7 @@ xtm_status xtm_particles_reset(xtm_particles P, int32_t turn, void* stream) {
     hipError_t e = launch_iota(P->idx[1 - P->cur], P->n, P->ctrl, (int32_t)P->n, turn, s);
     if (e == hipSuccess)
       e = launch_epilogue(P->idx[1 - P->cur], P->idx[P->cur], nullptr, P->n > 0 ? P->n : 1,
-                          soa_of(P), P->ctrl, P->blockcnt, P->passes, 0, 0, 0, s);
+                          soa_of(P), P->ctrl, P->blockcnt, P->passes, 0, 0, 0, 0, false, s);
     if (e != hipSuccess) return hip_fail(e, "alive-list rebuild");
     P->turn = turn;
     P->alive_upper = P->n;
@@ -1532,7 +1538,7 @@ xtm_status xtm_retire(xtm_particles P, const float* d_logit, float logit_thresho
     if (e == hipSuccess) e = launch_iota(P->idx[1 - P->cur], P->n, P->ctrl, (int32_t)P->n, P->turn, s);
     if (e == hipSuccess)
       e = launch_epilogue(P->idx[1 - P->cur], P->idx[P->cur], nullptr, P->n > 0 ? P->n : 1,
-                          soa_of(P), P->ctrl, P->blockcnt, P->passes, 0, 0, 0, s);
+                          soa_of(P), P->ctrl, P->blockcnt, P->passes, 0, 0, 0, 0, false, s);
     unsigned int hc[2] = {0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(hc, counts, sizeof hc, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -1690,7 +1696,7 @@ xtm_status xtm_resume_retired(xtm_lattice L, xtm_particles P, const xtm_track_op
     // every particle still alive is now at the horizon: rebuild the set's list
     HIP_TRY(launch_iota(P->idx[1 - P->cur], n, P->ctrl, (int32_t)n, horizon, s), "alive-list rebuild");
     HIP_TRY(launch_epilogue(P->idx[1 - P->cur], P->idx[P->cur], nullptr, n > 0 ? n : 1, soa_of(P),
-                            P->ctrl, P->blockcnt, P->passes, 0, 0, 0, s),
+                            P->ctrl, P->blockcnt, P->passes, 0, 0, 0, 0, false, s),
             "alive-list rebuild");
     P->turn = horizon;
     P->alive_upper = n;

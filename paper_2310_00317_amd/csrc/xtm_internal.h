@@ -89,8 +89,10 @@ void matched_gaussian(const NormalForm6& nf, double beta0, const double eps[3],
                       const double* gauss, int64_t n, double* out);
 
 // launch helpers implemented in xtm_kernels.hip; all are stream-ordered
+// words of a particle set's device counters, and where the 64-bit pass count lies
+constexpr int32_t kCtrlWords = 8, kCtrlPasses = 6;
 hipError_t launch_init(const double* coords6, int64_t n, int64_t first_id, SoA P, KernelRef r,
-                       hipStream_t s);
+                       int32_t* idx, int32_t* ctrl, int64_t* passes, hipStream_t s);
 hipError_t launch_iota(int32_t* idx, int64_t n, int32_t* ctrl, int32_t n_alive, int32_t turn,
                        hipStream_t s);
 hipError_t launch_advance(int32_t* ctrl, int32_t dk, hipStream_t s);
@@ -109,7 +111,7 @@ hipError_t launch_track(const uint64_t* tab, int32_t n_el, SoA P, const int32_t*
 hipError_t launch_epilogue(const int32_t* idx_in, int32_t* idx_out, int32_t* lost_out,
                            int64_t grid_upper, SoA P, int32_t* ctrl, int32_t* blockcnt,
                            int64_t* passes, int32_t n_el, int32_t chunk_turns, int32_t backward,
-                           hipStream_t s);
+                           int32_t dk, bool fresh, hipStream_t s);
 // coordinates of the particles in lost[0..ctrl[3]) re-tracked from the chunk
 // start to their loss point (for kernels that record losses in registers)
 hipError_t launch_track_batched(const uint64_t* const* tabs, const int32_t* first_slot, int32_t nv,
