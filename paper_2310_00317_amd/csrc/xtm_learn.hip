@@ -442,14 +442,6 @@ __global__ void __launch_bounds__(256) k_mlp_init(float* __restrict__ theta,
 // ------------------------------------------------------------- features
 constexpr int kWin = 512, kRecTurns = 1024;
 
-// x / b with r = 1/b rounded: product, exact remainder and correction instead
-// of the division's eleven operations (an infinite quotient stays one).
-__device__ __forceinline__ double div_by(double x, double b, double r) {
-  const double q = x * r;
-  const double c = fma(fma(-b, q, x), r, q);
-  return isinf(q) ? q : c;
-}
-
 // Three stages (half = stride, 2 stride, 4 stride) of the radix-2
 // decimation-in-time transform on eight elements `stride` apart, the first of
 // them at position `pos` of its group of `stride`: v0 +- w v1 with
@@ -583,7 +575,7 @@ __device__ float tune_of(FeatLds<G, T>& s) {
 // piece, and groups of neighbours are numbered within an XCD (blocks go round
 // the eight XCDs), whose L2 then holds the rest of each 128-byte line.
 // One particle per workgroup fetched every piece eight times over: 1,040 us
-// for 20,000 particles, 0.32 TB/s; now 192 us, 1.7 TB/s, the rest of the
+// for 20,000 particles, 0.32 TB/s; now 195 us, 1.7 TB/s, the rest of the
 // time being the FP64 actions and the transforms between the barriers.  Eight
 // butterflies' elements stay in registers for three stages, so a transform
 // crosses LDS three times, not nine (same operations in the same order).
@@ -608,16 +600,20 @@ __global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec
   const float* __restrict__ r = rec + ip;
   for (int k = threadIdx.x; k < kWin / 2; k += T) s.tw[k] = tw[k];
   for (int k = threadIdx.x; k < kWin; k += T) s.win[k] = win[k];
-  const double sbx = sqrt(bx), sby = sqrt(by), rsx = 1.0 / sbx, rsy = 1.0 / sby;
-  auto action = [](double x, double px, double a, double b, double sb, double rs, double& u,
+  // normalised coordinates u = x / sqrt(b), pu = (a x + b px) / sqrt(b) and the
+  // action (u^2 + pu^2) / 2, as (x^2 + (a x + b px)^2) / 2 b: products with the
+  // reciprocals instead of four quotients a turn (202 us -> 195 us)
+  const double rsx = 1.0 / sqrt(bx), rsy = 1.0 / sqrt(by), hbx = 0.5 / bx, hby = 0.5 / by;
+  auto action = [](double x, double px, double a, double b, double rs, double hb, double& u,
                    double& pu) {
-    u = div_by(x, sb, rs);
-    pu = div_by(a * x + b * px, sb, rs);
-    return 0.5 * (u * u + pu * pu);
+    const double l = fma(b, px, a * x);
+    u = x * rs;
+    pu = l * rs;
+    return fma(l, l, x * x) * hb;
   };
   double u, pu;
-  const double jx0 = action(r[0], r[n], ax, bx, sbx, rsx, u, pu);
-  const double jy0 = action(r[2 * n], r[3 * n], ay, by, sby, rsy, u, pu);
+  const double jx0 = action(r[0], r[n], ax, bx, rsx, hbx, u, pu);
+  const double jy0 = action(r[2 * n], r[3 * n], ay, by, rsy, hby, u, pu);
   // sums of j - j0 and its square, the first and last quarter's j; maxima
   double d1x = 0.0, d2x = 0.0, f0x = 0.0, f1x = 0.0, d1y = 0.0, d2y = 0.0, f0y = 0.0, f1y = 0.0;
   double r2max = 0.0, amax = 0.0;
@@ -626,6 +622,8 @@ __global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec
 #pragma unroll 1
   for (int h = 0; h < 2; ++h) {
     float2 zy[kBlk][8];
+    // sums of this half's first and second quarter
+    double lx = 0.0, ly = 0.0, hx = 0.0, hy = 0.0;
 #pragma unroll
     for (int b = 0; b < kBlk; ++b) {
       // elements 8 blk .. 8 blk + 7 of the bit-reversed order: turns 64 apart
@@ -640,20 +638,15 @@ __global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec
         const Off at = (Off)tb * 4 * (Off)n + (Off)ip;
         const double x = row[at], px = row[n + at], y = row[2 * n + at], py = row[3 * n + at];
         double ux, pux, uy, puy;
-        const double jx = action(x, px, ax, bx, sbx, rsx, ux, pux);
-        const double jy = action(y, py, ay, by, sby, rsy, uy, puy);
+        const double jx = action(x, px, ax, bx, rsx, hbx, ux, pux);
+        const double jy = action(y, py, ay, by, rsy, hby, uy, puy);
         const double dx = jx - jx0, dy = jy - jy0;
         d1x += dx;
         d2x = fma(dx, dx, d2x);
         d1y += dy;
         d2y = fma(dy, dy, d2y);
-        if (rk < 4) {
-          f0x += h == 0 ? jx : 0.0;
-          f0y += h == 0 ? jy : 0.0;
-        } else {
-          f1x += h == 1 ? jx : 0.0;
-          f1y += h == 1 ? jy : 0.0;
-        }
+        (rk < 4 ? lx : hx) += jx;
+        (rk < 4 ? ly : hy) += jy;
         r2max = fmax(r2max, x * x + y * y);
         amax = fmax(amax, jx + jy);
         const float wv = s.win[t];
@@ -661,13 +654,20 @@ __global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec
         zy[b][k] = make_float2(wv * (float)uy, -wv * (float)puy);
         // the sums are taken turn by turn (an empty constraint: the compiler
         // otherwise keeps every turn's actions in registers to sum them later)
-        asm volatile("" : "+v"(d1x), "+v"(d2x), "+v"(d1y), "+v"(d2y), "+v"(f0x), "+v"(f0y),
-                          "+v"(f1x), "+v"(f1y), "+v"(r2max), "+v"(amax));
+        asm volatile("" : "+v"(d1x), "+v"(d2x), "+v"(d1y), "+v"(d2y), "+v"(lx), "+v"(ly),
+                          "+v"(hx), "+v"(hy), "+v"(r2max), "+v"(amax));
       }
       fft_stages<1>(zx, 0, s.tw);
       fft_stages<1>(zy[b], 0, s.tw);
 #pragma unroll
       for (int k = 0; k < 8; ++k) s.z[8 * blk + k][p] = zx[k];
+    }
+    if (h == 0) {
+      f0x = lx;
+      f0y = ly;
+    } else {
+      f1x = hx;
+      f1y = hy;
     }
     __syncthreads();
     q[2 * h] = tune_of<G, T>(s);
