@@ -1414,18 +1414,20 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
     const int64_t wf = mlp_workspace_floats(bmax);
     float *work = nullptr, *loss = nullptr;
     int32_t* perm_d = nullptr;
+    double2* bias = nullptr;  // an epoch's Adam corrections
+    const int64_t nb = (n + batch - 1) / batch;
     auto release = [&]() {
-      hipFree(work); hipFree(loss); hipFree(perm_d);
+      hipFree(work); hipFree(loss); hipFree(perm_d); hipFree(bias);
     };
     if (hipMalloc(&work, wf * sizeof(float)) != hipSuccess ||
         hipMalloc(&loss, 4096 * sizeof(float)) != hipSuccess ||
-        hipMalloc(&perm_d, n * sizeof(int32_t)) != hipSuccess) {
+        hipMalloc(&perm_d, n * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&bias, nb * sizeof(double2)) != hipSuccess) {
       release();
       return fail(XTM_E_NOMEM, "training buffers");
     }
     std::vector<int32_t> perm(n);
     std::mt19937_64 rng(shuffle_seed);
-    const int64_t nb = (n + batch - 1) / batch;
     std::vector<float> lh;
     hipError_t e = hipSuccess;
     for (int32_t ep = 0; ep < epochs && e == hipSuccess; ++ep) {
@@ -1435,10 +1437,12 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
         std::swap(perm[i], perm[j]);
       }
       e = hipMemcpyAsync(perm_d, perm.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s);
+      if (e == hipSuccess) e = launch_adam_bias(bias, *step + 1, nb, s);
       for (int64_t b = 0; b < nb && e == hipSuccess; ++b) {
         const int64_t start = b * batch, B = (n - start < batch) ? n - start : batch;
         e = launch_mlp_train_step(d_theta, d_m, d_v, d_norm, d_x, d_y, perm_d + start, B,
-                                  pos_weight, ++*step, lr, loss + (b % 4096), work, s);
+                                  pos_weight, bias + b, lr, loss + (b % 4096), work, s);
+        ++*step;
       }
       // mean batch loss of the epoch (the permutation buffer is reused next epoch)
       if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -278,11 +278,13 @@ hipError_t launch_mlp_grad(const float* theta, const float* norm, const float* X
 hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int32_t step, float lr,
                        hipStream_t s);
 // One training step: gradient of the batch rows perm[0 .. B-1] of (X, Y) and
-// the Adam update, the loss into *loss.
+// the Adam update with the step's bias corrections *bias, the loss into *loss.
 hipError_t launch_mlp_train_step(float* theta, float* m, float* v, const float* norm,
                                  const float* X, const float* Y, const int32_t* perm, int64_t B,
-                                 float pos_weight, int32_t step, float lr, float* loss, float* work,
-                                 hipStream_t s);
+                                 float pos_weight, const double2* bias, float lr, float* loss,
+                                 float* work, hipStream_t s);
+// Adam's bias corrections (1 - b1^t, 1 - b2^t) of n steps t from first_step on.
+hipError_t launch_adam_bias(double2* bias, int32_t first_step, int64_t n, hipStream_t s);
 hipError_t launch_mlp_init(float* theta, unsigned long long seed, hipStream_t s);
 hipError_t launch_features(const float* rec, int64_t n, const double twiss4[4], double emit,
                            double r_ap, const float2* tw, const float* win, float* out,

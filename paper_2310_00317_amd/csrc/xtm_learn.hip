@@ -61,6 +61,10 @@ struct NetLds {
   float b3;
 };
 
+__device__ __forceinline__ float4 load4(const float* p) {
+  return make_float4(p[0], p[1], p[2], p[3]);
+}
+
 __device__ void load_net(NetLds& s, const float* __restrict__ th) {
   // group g: four rows of one column (neighbouring threads neighbouring columns)
   for (int g = threadIdx.x; g < kIn / 4 * kH; g += blockDim.x) {
@@ -68,11 +72,23 @@ __device__ void load_net(NetLds& s, const float* __restrict__ th) {
     const float* w = th + oW1 + 4 * q * kH + n;
     s.w1[n / 16][q * 16 + n % 16] = bf16_pack(w[0], w[kH], w[2 * kH], w[3 * kH]);
   }
-#pragma unroll 8
-  for (int g = threadIdx.x; g < kH / 4 * kH; g += blockDim.x) {
-    const int k4 = g / kH, n = g % kH;
-    const float* w = th + oW2 + 4 * k4 * kH + n;
-    s.w2[n / 16][k4 / 4][(k4 % 4) * 16 + n % 16] = bf16_pack(w[0], w[kH], w[2 * kH], w[3 * kH]);
+  // four rows of four columns at a time, a thread's sixteen 16-byte reads all in
+  // flight (256 threads)
+  float4 v[4][4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const int g = (int)threadIdx.x + 256 * m, k4 = g / (kH / 4), n = 4 * (g % (kH / 4));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[m][j] = load4(th + oW2 + (4 * k4 + j) * kH + n);
+  }
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const int g = (int)threadIdx.x + 256 * m, k4 = g / (kH / 4), n = 4 * (g % (kH / 4));
+    bf16x4* to = &s.w2[n / 16][k4 / 4][(k4 % 4) * 16 + n % 16];
+    to[0] = bf16_pack(v[m][0].x, v[m][1].x, v[m][2].x, v[m][3].x);
+    to[1] = bf16_pack(v[m][0].y, v[m][1].y, v[m][2].y, v[m][3].y);
+    to[2] = bf16_pack(v[m][0].z, v[m][1].z, v[m][2].z, v[m][3].z);
+    to[3] = bf16_pack(v[m][0].w, v[m][1].w, v[m][2].w, v[m][3].w);
   }
   for (int i = threadIdx.x; i < kH; i += blockDim.x) {
     s.b1[i] = th[oB1 + i];
@@ -93,10 +109,6 @@ __device__ __forceinline__ bf16x4 load_x(const float* __restrict__ X, int64_t ro
               x3 = on ? r[3] : 0.f;
   return bf16_pack((x0 - mean.x) * inv.x, (x1 - mean.y) * inv.y, (x2 - mean.z) * inv.z,
                    (x3 - mean.w) * inv.w);
-}
-
-__device__ __forceinline__ float4 load4(const float* p) {
-  return make_float4(p[0], p[1], p[2], p[3]);
 }
 
 // Activations of four neurons (16 nt + 4 q ..) of one sample: bias, ReLU, bf16.
@@ -183,7 +195,10 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ t
 // block's 64 rows.  What bounds it: latency, a block's chain from the weights
 // (75 KB) over three small products to its share of the partial gradient;
 // 81 us a call of 4,096 rows (16,384: 141) in the form that staged every
-// element through LDS, now 19 (16,384: 40), its reduction included.
+// element through LDS, now 20 (16,384: 38), its reduction included.  Every sum
+// keeps that form's order, so a training run gives the same bits (with the
+// logit's sum in another order, 3 % faster, the rounding of some activation
+// fell the other way after some tens of steps, and the weights went apart).
 struct GradLds {
   NetLds net;
   bf16x4 w2r[kTiles][kTiles][64];   // W2[16 mt + l % 16][16 kt + 4 q + j], own tiles mt
@@ -191,7 +206,8 @@ struct GradLds {
   bf16x4 dz2[4][kTiles][64];        // per wave: dZ2[4 q + j][16 nt + l % 16], own tiles nt
   bf16x4 dz1[4][kTiles][64];        // per wave: dZ1, own tiles
   unsigned short x[4][16][kIn + 4]; // per wave: rows of X (bf16)
-  float gb1[4][kH], gb2[4][kH], gw3[4][kH];  // per-wave column sums
+  unsigned short h2[kSamplesPerBlock][kH + 8];  // rows of H2 (bf16)
+  float gb1[4][kH];                 // per-wave column sums
   float dz3[4][16], lossv[4][16];
 };
 
@@ -209,19 +225,21 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int col = l & 15, q = l >> 4;
   const int own = kTiles / (int)gridDim.y, t0 = (int)blockIdx.y * own;  // own tiles t0 .. t0 + own
+  // the rows first: a row's place and then its words are two latencies, under
+  // the weights' one
+  const int64_t row = (int64_t)blockIdx.x * kSamplesPerBlock + 16 * w + col;  // this lane's sample
+  const bool on = row < B;
+  const int64_t src = on ? (perm ? perm[row] : row) : 0;
+  const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
+  const bf16x4 x = load_x(X, src, on, q, mean, inv);
+  const float y = on ? Y[src] : 0.f;
   load_net(s.net, theta);
   for (int g = threadIdx.x; g < own * 16 * (kH / 4); g += blockDim.x) {
     const int r = t0 * 16 + g / (kH / 4), c4 = g % (kH / 4);
     const float4 v = load4(theta + oW2 + r * kH + 4 * c4);
     s.w2r[r / 16][c4 / 4][(c4 % 4) * 16 + r % 16] = bf16_pack(v.x, v.y, v.z, v.w);
   }
-  const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
-  const int64_t row = (int64_t)blockIdx.x * kSamplesPerBlock + 16 * w + col;  // this lane's sample
-  const bool on = row < B;
-  const int64_t src = on ? (perm ? perm[row] : row) : 0;
-  const bf16x4 x = load_x(X, src, on, q, mean, inv);
   *reinterpret_cast<bf16x4*>(&s.x[w][col][4 * q]) = x;
-  const float y = on ? Y[src] : 0.f;
   __syncthreads();
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   bf16x4 h1t[kTiles];
@@ -234,7 +252,6 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
     s.h1[w][nt][l] =
         bf16_pack(relu(c[0] + b), relu(c[1] + b), relu(c[2] + b), relu(c[3] + b));
   }
-  float z = 0.f;
   bf16x4 h2t[kTiles];
 #pragma unroll
   for (int nt = 0; nt < kTiles; ++nt) {
@@ -242,12 +259,17 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
 #pragma unroll
     for (int kt = 0; kt < kTiles; ++kt) c = mfma16(s.net.w2[nt][kt][l], h1t[kt], c);
     h2t[nt] = activate(c, s.net.b2 + 16 * nt + 4 * q);
-    const float* w3 = s.net.w3 + 16 * nt + 4 * q;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) z += bf16_at(h2t[nt], j) * w3[j];
+    *reinterpret_cast<bf16x4*>(&s.h2[16 * w + col][16 * nt + 4 * q]) = h2t[nt];
   }
-  z += __shfl_xor(z, 16, 64);
-  z += __shfl_xor(z, 32, 64);
+  // the logit of this lane's sample, the neurons in order (training amplifies
+  // a rounding that falls the other way, so every sum of the step has one order)
+  float z = 0.f;
+#pragma unroll
+  for (int k = 0; k < kH; k += 4) {
+    const bf16x4 h = *reinterpret_cast<const bf16x4*>(&s.h2[16 * w + col][k]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z += bf16_at(h, j) * s.net.w3[k + j];
+  }
   z += s.net.b3;
   // dL/dz3 of this lane's sample (the four quads hold the same)
   float d = 0.f, lv = 0.f;
@@ -277,21 +299,13 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
     for (int j = 0; j < 4; ++j) v[j] = bf16_at(h2t[nt], j) > 0.f ? dq * w3[j] : 0.f;
     dz2t[nt] = bf16_pack(v[0], v[1], v[2], v[3]);
   }
-  // own tiles, samples down: H2, dZ2 (with the b2 and w3 sums), dZ1 (with b1's)
+  // own tiles, samples down: dZ2, and dZ1 with b1's sums
   for (int nt = t0; nt < t0 + own; ++nt) {
     const int n = 16 * nt + col;
-    f32x4 c = zero;
+    const float w3 = s.net.w3[n];
+    float v[4];
 #pragma unroll
-    for (int kt = 0; kt < kTiles; ++kt) c = mfma16(h1t[kt], s.net.w2[nt][kt][l], c);
-    const float b = s.net.b2[n], w3 = s.net.w3[n];
-    float v[4], gb2 = 0.f, gw3 = 0.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float h = bf16_value(relu(c[j] + b));
-      v[j] = h > 0.f ? dqr[j] * w3 : 0.f;
-      gb2 += v[j];
-      gw3 += h * dqr[j];
-    }
+    for (int j = 0; j < 4; ++j) v[j] = s.h2[16 * w + 4 * q + j][n] ? dqr[j] * w3 : 0.f;
     s.dz2[w][nt][l] = bf16_pack(v[0], v[1], v[2], v[3]);
     f32x4 g = zero;
 #pragma unroll
@@ -306,33 +320,36 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
     s.dz1[w][nt][l] = bf16_pack(v[0], v[1], v[2], v[3]);
     gb1 += __shfl_xor(gb1, 16, 64);
     gb1 += __shfl_xor(gb1, 32, 64);
-    gb2 += __shfl_xor(gb2, 16, 64);
-    gb2 += __shfl_xor(gb2, 32, 64);
-    gw3 += __shfl_xor(gw3, 16, 64);
-    gw3 += __shfl_xor(gw3, 32, 64);
-    if (q == 0) {
-      s.gb1[w][n] = gb1;
-      s.gb2[w][n] = gb2;
-      s.gw3[w][n] = gw3;
-    }
+    if (q == 0) s.gb1[w][n] = gb1;
   }
   __syncthreads();
   float* g = part + (size_t)blockIdx.x * kParams;
-  for (int n = 16 * t0 + (int)threadIdx.x; n < 16 * (t0 + own); n += blockDim.x) {
+  for (int n = 16 * t0 + (int)threadIdx.x; n < 16 * (t0 + own); n += blockDim.x)
     g[oB1 + n] = ((s.gb1[0][n] + s.gb1[1][n]) + s.gb1[2][n]) + s.gb1[3][n];
-    g[oB2 + n] = ((s.gb2[0][n] + s.gb2[1][n]) + s.gb2[2][n]) + s.gb2[3][n];
-    g[oW3 + n] = ((s.gw3[0][n] + s.gw3[1][n]) + s.gw3[2][n]) + s.gw3[3][n];
+  // own columns' b2 and w3 sums, the block's b3 and loss: rows in order
+  const int cols = 16 * own;
+  if ((int)threadIdx.x < 2 * cols) {
+    const bool for_w3 = (int)threadIdx.x >= cols;
+    const int n = 16 * t0 + (for_w3 ? (int)threadIdx.x - cols : (int)threadIdx.x);
+    const float w3 = s.net.w3[n];
+    float acc = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < kSamplesPerBlock; ++r) {
+      const float dr = bf16_value(s.dz3[r / 16][r % 16]);
+      const unsigned short h = s.h2[r][n];
+      const float hw = __uint_as_float((unsigned int)h << 16) * dr, hb = h ? dr * w3 : 0.f;
+      acc += for_w3 ? hw : hb;
+    }
+    g[(for_w3 ? oW3 : oB2) + n] = acc;
   }
-  if (w == 0 && blockIdx.y == 0) {  // lanes 0..63: the block's samples
-    float gb3 = s.dz3[q][col], ls = s.lossv[q][col];
-    for (int o = 32; o > 0; o >>= 1) {
-      gb3 += __shfl_xor(gb3, o, 64);
-      ls += __shfl_xor(ls, o, 64);
-    }
-    if (l == 0) {
-      g[oB3] = gb3;
-      loss_part[blockIdx.x] = ls;
-    }
+  if (blockIdx.y == 0 && (threadIdx.x == 191 || threadIdx.x == 255)) {
+    const bool for_loss = threadIdx.x == 255;
+    const float* v = for_loss ? &s.lossv[0][0] : &s.dz3[0][0];
+    float acc = 0.f;
+#pragma unroll 16
+    for (int r = 0; r < kSamplesPerBlock; ++r) acc += v[r];
+    if (for_loss) loss_part[blockIdx.x] = acc;
+    else g[oB3] = acc;
   }
   // W2[j1][n2] = sum_s H1[s][j1] dZ2[s][n2], own n2 tiles, in steps of 16 rows
   for (int t = w; t < kTiles * own; t += 4) {
@@ -358,18 +375,18 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
   }
 }
 
-// Sum over blocks b = 0..nb-1 (in order) of part[b][i]: the loads of sixteen
+// Sum over blocks b = 0..nb-1 (in order) of part[b][i]: the loads of 32
 // partials in flight at a time (the sums of one parameter are one chain).
 __device__ __forceinline__ float sum_parts(const float* __restrict__ part, int nb, size_t stride,
                                            int i) {
   float acc = 0.f;
   int b = 0;
-  for (; b + 16 <= nb; b += 16) {
-    float v[16];
+  for (; b + 32 <= nb; b += 32) {
+    float v[32];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = part[(size_t)(b + k) * stride + i];
+    for (int k = 0; k < 32; ++k) v[k] = part[(size_t)(b + k) * stride + i];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) acc += v[k];
+    for (int k = 0; k < 32; ++k) acc += v[k];
   }
   for (; b < nb; ++b) acc += part[(size_t)b * stride + i];
   return acc;
@@ -386,31 +403,38 @@ __global__ void __launch_bounds__(64) k_mlp_reduce(const float* __restrict__ par
 
 // Adam (Kingma & Ba): m <- b1 m + (1-b1) g, v <- b2 v + (1-b2) g^2,
 // theta <- theta - lr mhat / (sqrt(vhat) + eps), bias-corrected with step t >= 1
-// (c1 = 1 - b1^t, c2 = 1 - b2^t, from the host).  The update is evaluated in
+// (c.x = 1 - b1^t, c.y = 1 - b2^t; a training epoch's from one launch).  The update is evaluated in
 // FP64 from the FP32 masters and moments (b1 = 0.9, b2 = 0.999 exactly, not
 // their FP32 roundings) and stored back in FP32.
-struct AdamStep {
-  double b1, b2, eps, c1, c2;
-  float lr;
-};
+constexpr double kB1 = 0.9, kB2 = 0.999, kEps = 1e-8;
+
+__device__ __forceinline__ double2 adam_bias(int step) {
+  return make_double2(1.0 - pow(kB1, (double)step), 1.0 - pow(kB2, (double)step));
+}
+
+__global__ void __launch_bounds__(256) k_adam_bias(double2* __restrict__ c, int first, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) c[i] = adam_bias(first + i);
+}
 
 __device__ __forceinline__ void adam_update(float* __restrict__ theta, float* __restrict__ m,
                                             float* __restrict__ v, int i, double g,
-                                            const AdamStep& a) {
-  const double mi = a.b1 * (double)m[i] + (1.0 - a.b1) * g;
-  const double vi = a.b2 * (double)v[i] + (1.0 - a.b2) * g * g;
+                                            const double2& c, float lr) {
+  const double mi = kB1 * (double)m[i] + (1.0 - kB1) * g;
+  const double vi = kB2 * (double)v[i] + (1.0 - kB2) * g * g;
   m[i] = (float)mi;
   v[i] = (float)vi;
-  const double mh = mi / a.c1;
-  const double vh = vi / a.c2;
-  theta[i] = (float)((double)theta[i] - (double)a.lr * mh / (sqrt(vh) + a.eps));
+  const double mh = mi / c.x;
+  const double vh = vi / c.y;
+  theta[i] = (float)((double)theta[i] - (double)lr * mh / (sqrt(vh) + kEps));
 }
 
 __global__ void __launch_bounds__(64) k_adam(float* __restrict__ theta, float* __restrict__ m,
                                              float* __restrict__ v,
-                                             const float* __restrict__ grad, AdamStep a) {
+                                             const float* __restrict__ grad, int step,
+                                             float lr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kParams) adam_update(theta, m, v, i, grad[i], a);
+  if (i < kParams) adam_update(theta, m, v, i, grad[i], adam_bias(step), lr);
 }
 
 // The reduction of a training step and its update in one launch (the training
@@ -420,9 +444,11 @@ __global__ void __launch_bounds__(64) k_mlp_reduce_adam(const float* __restrict_
                                                         float* __restrict__ loss, int64_t B,
                                                         float* __restrict__ theta,
                                                         float* __restrict__ m,
-                                                        float* __restrict__ v, AdamStep a) {
+                                                        float* __restrict__ v,
+                                                        const double2* __restrict__ bias,
+                                                        float lr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kParams) adam_update(theta, m, v, i, sum_parts(part, nb, kParams, i), a);
+  if (i < kParams) adam_update(theta, m, v, i, sum_parts(part, nb, kParams, i), *bias, lr);
   if (i == kParams && loss) *loss = sum_parts(loss_part, nb, 1, 0) / (float)B;
 }
 
@@ -898,13 +924,6 @@ void enqueue_grad(const float* theta, const float* norm, const float* X, const f
                      X, Y, perm, B, pos_weight, work, work + (size_t)nb * kParams);
 }
 
-AdamStep adam_step(int32_t step, float lr) {
-  AdamStep a{0.9, 0.999, 1e-8, 0.0, 0.0, lr};
-  a.c1 = 1.0 - std::pow(a.b1, (double)step);
-  a.c2 = 1.0 - std::pow(a.b2, (double)step);
-  return a;
-}
-
 constexpr unsigned kParamBlocks = (kParams + 1 + 63) / 64;  // one thread more: the loss
 }  // namespace
 
@@ -924,21 +943,28 @@ hipError_t launch_mlp_grad(const float* theta, const float* norm, const float* X
 hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int32_t step, float lr,
                        hipStream_t s) {
   hipLaunchKernelGGL(k_adam, dim3(kParamBlocks), dim3(64), 0, s, theta, m, v, grad,
-                     adam_step(step, lr));
+                     step, lr);
+  return hipGetLastError();
+}
+
+hipError_t launch_adam_bias(double2* bias, int32_t first_step, int64_t n, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_adam_bias, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, bias,
+                     first_step, (int)n);
   return hipGetLastError();
 }
 
 hipError_t launch_mlp_train_step(float* theta, float* m, float* v, const float* norm,
                                  const float* X, const float* Y, const int32_t* perm, int64_t B,
-                                 float pos_weight, int32_t step, float lr, float* loss, float* work,
-                                 hipStream_t s) {
+                                 float pos_weight, const double2* bias, float lr, float* loss,
+                                 float* work, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   const int nb = (int)((B + kSamplesPerBlock - 1) / kSamplesPerBlock);
   enqueue_grad(theta, norm, X, Y, perm, B, pos_weight, work, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_mlp_reduce_adam, dim3(kParamBlocks), dim3(64), 0, s, work, nb,
-                     work + (size_t)nb * kParams, loss, B, theta, m, v, adam_step(step, lr));
+                     work + (size_t)nb * kParams, loss, B, theta, m, v, bias, lr);
   return hipGetLastError();
 }
 
