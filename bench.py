@@ -48,10 +48,10 @@ TRAFFIC_SOURCES = ("xtm_jit.cpp", "xtm_maps.h")
 MEASURED_TRAFFIC = {
     # (workload, particles, turns per step, kernel variant, source hash):
     #     (bytes per launch, profile)
-    ("cfg2", 100000, 1000, 14, "8fc270e379fe13d4"):
-        (21432430.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
-    ("cfg1sat", 1048576, 1000, 14, "8fc270e379fe13d4"):
-        (189155935.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
+    ("cfg2", 100000, 1000, 14, "82a15791a373ae66"):
+        (21813952.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
+    ("cfg1sat", 1048576, 1000, 14, "82a15791a373ae66"):
+        (189331730.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
 }
 
 
@@ -238,7 +238,10 @@ def refine_bench(args):
     state = parts.state[:n]
     n_lost = int((state == 0).sum().item())
     total_tests = int(tests.to(torch.int64).sum().item())
-    flops_per_test = 6 * M + 26
+    # position, fraction and line frame 26; of the polygon the edges that the
+    # test's ray meets, two around the beam: four interpolated coordinates, the
+    # crossing's two products and their difference, two compares each
+    flops_per_test = 26 + 2 * 17
     avg_ms = kernel_ms / max(steps, 1)
     value = n_lost / (avg_ms / 1e3) if avg_ms > 0 else 0.0
     achieved = total_tests * flops_per_test / (avg_ms / 1e3) / 1e12 if avg_ms > 0 else 0.0
@@ -310,7 +313,7 @@ def twiss_bench(args):
     ms = wall / steps * 1e3
     f = element_flops(el)
     f[np.isin(el["type"], (I.AP_CIRCLE, I.AP_ELLIPSE, I.AP_RECT))] = 0.0
-    turns = (tw["iterations"] + 1) * 9 + 11  # particle-turns per call
+    turns = (tw["iterations"] + 1) * 11  # particle-turns per call
     flops = turns * float(f.sum())
     achieved = flops / (ms / 1e3) / 1e12
     out = {
@@ -331,8 +334,8 @@ def twiss_bench(args):
                    "n_elements": len(el), "newton_steps": tw["iterations"],
                    "particle_turns": turns, "qx": tw["qx"], "qy": tw["qy"], "wall_s": wall},
         "roofline": {"bound": "alu", "kernel": "xtm_record (generated recording kernel, one "
-                                               "thread per particle, 9 or 11 particles: one "
-                                               "wave, latency-bound)",
+                                               "thread per particle, 11 particles: one wave, "
+                                               "latency-bound)",
                      "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": None,
                      "flops_per_call": flops},
