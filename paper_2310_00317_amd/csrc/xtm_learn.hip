@@ -24,6 +24,7 @@
 namespace xtm {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // parameter vector layout (FP32): W1[16][128], b1[128], W2[128][128], b2[128], w3[128], b3
@@ -37,10 +38,18 @@ constexpr int kTiles = kH / 16;       // 16-neuron tiles of a hidden layer
 __device__ __forceinline__ float bf16_value(float f) {  // rounded to bf16, as FP32
   return (float)(__bf16)f;
 }
+// Two values to a conversion (written value by value, the compiler converts
+// each alone and merges the pairs with a permute: three operations for one).
 __device__ __forceinline__ bf16x4 bf16_pack(float a, float b, float c, float d) {
-  typedef __bf16 b4 __attribute__((ext_vector_type(4)));
-  const b4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+  const u2 v = {__builtin_bit_cast(unsigned int, __builtin_convertvector((f2{a, b}), b2)),
+                __builtin_bit_cast(unsigned int, __builtin_convertvector((f2{c, d}), b2))};
   return __builtin_bit_cast(bf16x4, v);
+}
+__device__ __forceinline__ bf16x8 bf16_join(bf16x4 lo, bf16x4 hi) {
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 __device__ __forceinline__ float bf16_at(bf16x4 v, int j) {
   return __uint_as_float((unsigned int)(unsigned short)v[j] << 16);
@@ -50,13 +59,14 @@ __device__ __forceinline__ f32x4 mfma16(bf16x4 a, bf16x4 b, f32x4 c) {
 }
 
 // The forward network in LDS, the weights as operand fragments (8 bytes per
-// lane, 64 lanes of a fragment side by side: one conflict-free read each).
-// Lane l of a fragment holds four consecutive k of its column l % 16:
-//   w1[nt][l]      W1[4 q + j][16 nt + l % 16]            (q = l / 16)
-//   w2[nt][kt][l]  W2[16 kt + 4 q + j][16 nt + l % 16]
+// lane, 64 lanes of a fragment side by side: conflict-free reads; W2's in pairs,
+// 16 bytes a read).  Lane l of a fragment holds four consecutive k of its column
+// l % 16:
+//   w1[nt][l]         W1[4 q + j][16 nt + l % 16]            (q = l / 16)
+//   w2[nt][kt / 2][l] W2[16 kt + 4 q + j][16 nt + l % 16], kt even low, odd high
 struct NetLds {
   bf16x4 w1[kTiles][64];
-  bf16x4 w2[kTiles][kTiles][64];
+  bf16x8 w2[kTiles][kTiles / 2][64];
   float b1[kH], b2[kH], w3[kH];  // w3 already rounded to bf16 values
   float b3;
 };
@@ -72,23 +82,29 @@ __device__ void load_net(NetLds& s, const float* __restrict__ th) {
     const float* w = th + oW1 + 4 * q * kH + n;
     s.w1[n / 16][q * 16 + n % 16] = bf16_pack(w[0], w[kH], w[2 * kH], w[3 * kH]);
   }
-  // four rows of four columns at a time, a thread's sixteen 16-byte reads all in
+  // eight rows of four columns at a time, a thread's sixteen 16-byte reads all in
   // flight (256 threads)
-  float4 v[4][4];
+  float4 v[2][8];
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int g = (int)threadIdx.x + 256 * m, k4 = g / (kH / 4), n = 4 * (g % (kH / 4));
+  for (int m = 0; m < 2; ++m) {
+    const int g = (int)threadIdx.x + 256 * m, k8 = g / (kH / 4), n = 4 * (g % (kH / 4));
+    const int k = 32 * (k8 / 4) + 4 * (k8 % 4);  // rows k .. k + 3 and k + 16 .. k + 19
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[m][j] = load4(th + oW2 + (4 * k4 + j) * kH + n);
+    for (int j = 0; j < 8; ++j) v[m][j] = load4(th + oW2 + (k + j % 4 + 16 * (j / 4)) * kH + n);
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    const int g = (int)threadIdx.x + 256 * m, k4 = g / (kH / 4), n = 4 * (g % (kH / 4));
-    bf16x4* to = &s.w2[n / 16][k4 / 4][(k4 % 4) * 16 + n % 16];
-    to[0] = bf16_pack(v[m][0].x, v[m][1].x, v[m][2].x, v[m][3].x);
-    to[1] = bf16_pack(v[m][0].y, v[m][1].y, v[m][2].y, v[m][3].y);
-    to[2] = bf16_pack(v[m][0].z, v[m][1].z, v[m][2].z, v[m][3].z);
-    to[3] = bf16_pack(v[m][0].w, v[m][1].w, v[m][2].w, v[m][3].w);
+  for (int m = 0; m < 2; ++m) {
+    const int g = (int)threadIdx.x + 256 * m, k8 = g / (kH / 4), n = 4 * (g % (kH / 4));
+    bf16x8* to = &s.w2[n / 16][k8 / 4][(k8 % 4) * 16 + n % 16];
+    const float4* r = v[m];
+    to[0] = bf16_join(bf16_pack(r[0].x, r[1].x, r[2].x, r[3].x),
+                      bf16_pack(r[4].x, r[5].x, r[6].x, r[7].x));
+    to[1] = bf16_join(bf16_pack(r[0].y, r[1].y, r[2].y, r[3].y),
+                      bf16_pack(r[4].y, r[5].y, r[6].y, r[7].y));
+    to[2] = bf16_join(bf16_pack(r[0].z, r[1].z, r[2].z, r[3].z),
+                      bf16_pack(r[4].z, r[5].z, r[6].z, r[7].z));
+    to[3] = bf16_join(bf16_pack(r[0].w, r[1].w, r[2].w, r[3].w),
+                      bf16_pack(r[4].w, r[5].w, r[6].w, r[7].w));
   }
   for (int i = threadIdx.x; i < kH; i += blockDim.x) {
     s.b1[i] = th[oB1 + i];
@@ -100,13 +116,16 @@ __device__ void load_net(NetLds& s, const float* __restrict__ th) {
 
 __device__ __forceinline__ float relu(float z) { return z > 0.f ? z : 0.f; }
 
-// Standardised inputs of row `row` (zeros when `on` is false), features
-// 4 q .. 4 q + 3: the operand of one lane.
-__device__ __forceinline__ bf16x4 load_x(const float* __restrict__ X, int64_t row, bool on, int q,
-                                         const float4& mean, const float4& inv) {
-  const float* r = X + (on ? row : 0) * kIn + 4 * q;
-  const float x0 = on ? r[0] : 0.f, x1 = on ? r[1] : 0.f, x2 = on ? r[2] : 0.f,
-              x3 = on ? r[3] : 0.f;
+// Features 4 q .. 4 q + 3 of row `row`; the first row's when `on` is false (a
+// read every lane can do, so the rows' reads need no branches).
+__device__ __forceinline__ float4 read_x(const float* __restrict__ X, int64_t row, bool on, int q) {
+  return load4(X + (on ? row : 0) * kIn + 4 * q);
+}
+
+// Standardised inputs (of zeros when `on` is false): the operand of one lane.
+__device__ __forceinline__ bf16x4 standard_x(const float4& x, bool on, const float4& mean,
+                                             const float4& inv) {
+  const float x0 = on ? x.x : 0.f, x1 = on ? x.y : 0.f, x2 = on ? x.z : 0.f, x3 = on ? x.w : 0.f;
   return bf16_pack((x0 - mean.x) * inv.x, (x1 - mean.y) * inv.y, (x2 - mean.z) * inv.z,
                    (x3 - mean.w) * inv.w);
 }
@@ -119,29 +138,47 @@ __device__ __forceinline__ bf16x4 activate(const f32x4& c, const float* bias) {
 
 // Forward pass, T tiles of 16 rows per wave: both layers as weights^T times
 // activations^T, so a layer's D (neurons down, samples across) is the next
-// layer's B operand.  What bounds it: 64 fragment reads of 512 bytes from LDS
-// and 72 T matrix instructions per 16 T rows, and the rows once from HBM;
-// T = 4 shares each fragment read among four products: 84 us for 2^20 rows,
-// 0.47 PFLOP/s, against 760 us, 51 TFLOP/s, when every operand was staged
-// element by element through LDS.  Each block loads the network once and then runs tiles
-// blockIdx.x, blockIdx.x + gridDim.x, ...
+// layer's B operand.  Each block loads the network once and then runs tiles
+// blockIdx.x, blockIdx.x + gridDim.x, ...  T = 4 shares each fragment read among
+// four products.
+//   What bounds it: 72 matrix instructions a tile, 31 us for 2^20 rows at their
+// rate, and about as long in vector instructions (bias, ReLU, rounding, output
+// layer).  A layer-2 tile is therefore activated while the next one's products
+// run (three vector instructions to a product); the products go to vector
+// registers (with room for one wave a SIMD, the compiler takes accumulation
+// registers and copies every value out); the rows come a pass ahead.
+//   us for 2^20 rows: 757 when every operand was staged element by element
+// through LDS; 83 with the fragments; 63 with conversions and fragments in pairs,
+// the products in vector registers and the rows ahead; 54, 0.71 PFLOP/s, with
+// the activation between the products.  Two tiles a wave and twice the waves do
+// not replace that: 57.  The 32-deep product would give 12 us less, but adds in
+// another order, and some hidden values then round the other way.
+//   __launch_bounds__: two waves a SIMD.
 template <int T>
-__global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ theta,
+__global__ void __launch_bounds__(256, 2) k_mlp_forward(const float* __restrict__ theta,
                                                      const float* __restrict__ norm,
                                                      const float* __restrict__ X, int64_t B,
                                                      float* __restrict__ logit) {
   __shared__ NetLds net;
-  load_net(net, theta);
-  __syncthreads();
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int col = l & 15, q = l >> 4;
   const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
-  const int64_t per_block = 64 * T;
-  for (int64_t base = blockIdx.x * per_block; base < B; base += gridDim.x * per_block) {
-    const int64_t s0 = base + (int64_t)w * 16 * T + col;
+  const int64_t per_block = 64 * T, step = gridDim.x * per_block;
+  int64_t s0 = blockIdx.x * per_block + w * 16 * T + col;  // this lane's first sample
+  float4 in[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) in[t] = read_x(X, s0 + 16 * t, s0 + 16 * t < B, q);
+  load_net(net, theta);
+  __syncthreads();
+  for (int64_t base = blockIdx.x * per_block; base < B; base += step, s0 += step) {
     bf16x4 x[T], h[T][kTiles];
 #pragma unroll
-    for (int t = 0; t < T; ++t) x[t] = load_x(X, s0 + 16 * t, s0 + 16 * t < B, q, mean, inv);
+    for (int t = 0; t < T; ++t) x[t] = standard_x(in[t], s0 + 16 * t < B, mean, inv);
+    if (base + step < B) {  // the next pass's rows, under this one's products
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+        in[t] = read_x(X, s0 + step + 16 * t, s0 + step + 16 * t < B, q);
+    }
 #pragma unroll
     for (int nt = 0; nt < kTiles; ++nt) {
       const bf16x4 a = net.w1[nt][l];
@@ -154,25 +191,43 @@ __global__ void __launch_bounds__(256) k_mlp_forward(const float* __restrict__ t
     float z[T];
 #pragma unroll
     for (int t = 0; t < T; ++t) z[t] = 0.f;
-#pragma unroll 1
-    for (int nt = 0; nt < kTiles; ++nt) {
-      f32x4 c[T];
-#pragma unroll
-      for (int t = 0; t < T; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kt = 0; kt < kTiles; ++kt) {
-        const bf16x4 a = net.w2[nt][kt][l];
-#pragma unroll
-        for (int t = 0; t < T; ++t) c[t] = mfma16(a, h[t][kt], c[t]);
-      }
+    f32x4 p[T];  // the tile before, activated between this one's products
+    const auto finish = [&](int nt) {
       const float* w3 = net.w3 + 16 * nt + 4 * q;
 #pragma unroll
       for (int t = 0; t < T; ++t) {
-        const bf16x4 v = activate(c[t], net.b2 + 16 * nt + 4 * q);
+        const bf16x4 v = activate(p[t], net.b2 + 16 * nt + 4 * q);
 #pragma unroll
         for (int j = 0; j < 4; ++j) z[t] += bf16_at(v, j) * w3[j];
       }
+    };
+    const auto products = [&](int nt, f32x4* c) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) c[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kt = 0; kt < kTiles; kt += 2) {
+        const bf16x8 a = net.w2[nt][kt / 2][l];
+#pragma unroll
+        for (int t = 0; t < T; ++t) c[t] = mfma16(a.lo, h[t][kt], c[t]);
+#pragma unroll
+        for (int t = 0; t < T; ++t) c[t] = mfma16(a.hi, h[t][kt + 1], c[t]);
+      }
+    };
+    products(0, p);
+#pragma unroll 1
+    for (int nt = 1; nt < kTiles; ++nt) {
+      f32x4 c[T];
+      products(nt, c);
+      finish(nt - 1);
+#pragma unroll
+      for (int t = 0; t < T; ++t) p[t] = c[t];
+#pragma unroll
+      for (int i = 0; i < kTiles * T; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);  // a product
+        __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);  // three vector operations
+      }
     }
+    finish(kTiles - 1);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       float v = z[t];
@@ -231,7 +286,7 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
   const bool on = row < B;
   const int64_t src = on ? (perm ? perm[row] : row) : 0;
   const float4 mean = load4(norm + 4 * q), inv = load4(norm + kIn + 4 * q);
-  const bf16x4 x = load_x(X, src, on, q, mean, inv);
+  const bf16x4 x = standard_x(read_x(X, src, on, q), on, mean, inv);
   const float y = on ? Y[src] : 0.f;
   load_net(s.net, theta);
   for (int g = threadIdx.x; g < own * 16 * (kH / 4); g += blockDim.x) {
@@ -257,7 +312,10 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
   for (int nt = 0; nt < kTiles; ++nt) {
     f32x4 c = zero;
 #pragma unroll
-    for (int kt = 0; kt < kTiles; ++kt) c = mfma16(s.net.w2[nt][kt][l], h1t[kt], c);
+    for (int kt = 0; kt < kTiles; kt += 2) {
+      const bf16x8 a = s.net.w2[nt][kt / 2][l];
+      c = mfma16(a.hi, h1t[kt + 1], mfma16(a.lo, h1t[kt], c));
+    }
     h2t[nt] = activate(c, s.net.b2 + 16 * nt + 4 * q);
     *reinterpret_cast<bf16x4*>(&s.h2[16 * w + col][16 * nt + 4 * q]) = h2t[nt];
   }
@@ -862,12 +920,14 @@ hipError_t launch_mlp_forward(const float* theta, const float* norm, const float
                               float* logit, hipStream_t s) {
   if (B <= 0) return hipSuccess;
   // four tiles a wave once that still gives every CU a block (2^16 rows: 256
-  // blocks), one before; at most four blocks per CU, each of which loads the
-  // network once.  us for 16,384 / 2^17 / 2^20 rows: 13 / 17 / 88 (a call; 29 /
-  // 108 / 757 with one block per 64 rows and the staging of every operand).
+  // blocks), one before; at most the two blocks per CU that are resident at once,
+  // each of which loads the network once (1,024 blocks: 66 us for 2^20 rows, 512: 63,
+  // before the activation moved between the products).  us a call for 16,384 /
+  // 2^17 / 2^20 rows: 13 / 10.5 / 55 (29 / 108 / 757 with one block per 64 rows and
+  // the staging of every operand).
   if (B >= 65536) {
     const int64_t nb = (B + 255) / 256;
-    hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)(nb < 1024 ? nb : 1024)), dim3(256), 0, s,
+    hipLaunchKernelGGL(k_mlp_forward<4>, dim3((unsigned)(nb < 512 ? nb : 512)), dim3(256), 0, s,
                        theta, norm, X, B, logit);
   } else {
     hipLaunchKernelGGL(k_mlp_forward<1>, dim3((unsigned)((B + 63) / 64)), dim3(256), 0, s, theta,

@@ -17,10 +17,11 @@ def test_forward_tiles(P, oracle_mod, B):
     L.test_mlp_forward_matches_oracle(P, B)
 
 
-@pytest.mark.parametrize("B", [65535, 65536, 65537, 65793, 262145])
+@pytest.mark.parametrize("B", [65535, 65536, 65537, 65793, 131072, 131073, 262145])
 def test_forward_large_batches(P, oracle_mod, B):
     """One tile of 16 rows per wave below 65,536 rows, four from there on; more
-    than 1,024 workgroups' worth of rows above 262,144.  Every row is the same
+    than 512 workgroups' worth of rows (a pass's, the next read ahead) above
+    131,072.  Every row is the same
     sums in the same order in both forms: the same bits as in batches of the
     size that is held against the oracle.  (Against the oracle itself, among
     65,535 rows of 256 rounded activations some round the other way than in
