@@ -179,10 +179,15 @@ struct LineKernel {
   int32_t* cells_d = nullptr;  // per cell: kind, first parameter word, first element, words
   std::string source;
   std::string error;
-  // the wide form of the same kernel, on the same arrays (build_wide_form)
+  // the wide form of the same kernel (build_wide_form); until it is built, the
+  // parameters, each element's signature and its first word, on the host
   std::string wide_source;
+  std::vector<double> wide_prm;
+  std::vector<uint32_t> wide_sig;
+  std::vector<int32_t> wide_word;
   bool wide_tried = false;
   hipFunction_t wide_fn = nullptr;
+  double* wide_prm_d = nullptr;
 };
 // Generated-kernel forms ("styles"), all computing the same maps in the same
 // order: the workgroup (256 lanes or one wave), the way element code reads

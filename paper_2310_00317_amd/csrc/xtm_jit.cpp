@@ -71,6 +71,14 @@ constexpr int kLongCode = 64;
 // less costs the last overlap (thick ring, 30,000: 3.48e11 at every drift,
 // 3.65e11-3.80e11 at every second to fourth)
 constexpr int32_t kSettleWords = 12;
+// parameter words that a cell of the wide form holds in scalar registers (two
+// a word, of 102): an element's words are read further ahead of it only while
+// those of the elements in between fit, else at the element itself.  Without
+// the limit the registers are spilled in the middle of a cell that has several
+// high-order multipoles in a row (three of order 10 and a drift: 201 lane moves
+// among 2,110 instructions, with it 77 among 1,984); the listed rings, two of
+// order 10 in a row among them, take the same time either way
+constexpr int32_t kScalarWords = 24;
 // cells ahead of the tracking wave that the recording kernel's other wave loads
 constexpr int32_t kAhead = 4;
 
@@ -165,17 +173,22 @@ int32_t n_words(uint32_t s) {
 // sequences do not serve, set `bad`.
 // kTest: the generic drift, and a loss test's result in `ok` with the state a
 // lost particle takes in `ls`.
-// kFlagScalar: as kFlag, the parameters in scalar registers.
+// kFlagScalar, kTestScalar: as kFlag and kTest from the wide form's parameters
+// (wide_words), the former's in scalar registers.
 enum EmitMode {
-  kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kFlag = 4, kTest = 5, kFlagScalar = 6
+  kSaveAtLoss = 0, kMarkOnly = 1, kReplay = 2, kFlag = 4, kTest = 5, kFlagScalar = 6,
+  kTestScalar = 7
 };
 
+// batched: for a kernel that serves a batch of lattice variants.
 std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool far_rf,
-                 EmitMode mode) {
+                 EmitMode mode, bool batched = false) {
   const uint32_t kt = s & 0xffu, order = (s >> 8) & 0xffu;
   auto P = [&](int32_t m) { return "(" + arr + ")[" + std::to_string(m) + "]"; };
   const bool flag = mode == kFlag || mode == kFlagScalar;
-  const std::string sc = mode == kFlagScalar ? ", true" : "";  // multipole's second parameter
+  const bool negated = mode == kFlagScalar || mode == kTestScalar;
+  // multipole's second parameter (a batch's slot partition takes scalar registers)
+  const std::string sc = !negated ? "" : batched ? ", 2" : ", 1";
   // the radiation step of a multipole whose radiation length is word m
   auto radiation = [&](int32_t m) {
     return flag && (s & kRecip)
@@ -192,9 +205,9 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       else if (flag)
         c << "xtmm::drift_flag<" << (mode == kFlagScalar ? "true" : "false") << ">(q, " << P(0)
           << ", " << any << ", a_min, bad);";
-      else if (mode == kTest)
+      else if (mode == kTest || mode == kTestScalar)
         c << "{ const xtmm::DriftIn d_ = xtmm::drift_in(q); double lp_, dq_; "
-          << "xtmm::drift_generic(" << P(0) << ", d_, lp_, dq_); "
+          << "xtmm::drift_generic(" << (negated ? "-" : "") << P(0) << ", d_, lp_, dq_); "
           << "xtmm::drift_apply(q, lp_, dq_); ok = d_.pz2 > 0.0; ls = -1; }";
       else if (mode == kMarkOnly)
         c << "xtmm::mark(xtmm::drift_exact(q, " << P(0) << ", " << any << "), code, st, e0 + "
@@ -232,8 +245,8 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       break;
     }
     case K_RF:
-      c << (far_rf ? "xtmm::rf_far(q, " : "xtmm::rf(q, ") << P(0) << ", " << P(1) << ", " << P(2)
-        << ", beta0, two_over_beta0);";
+      c << (far_rf ? "xtmm::rf_far(q, " : negated ? "xtmm::rf<xtmm::kByVector>(q, " : "xtmm::rf(q, ")
+        << P(0) << ", " << P(1) << ", " << P(2) << ", beta0, two_over_beta0);";
       if (flag)
         c << " bad |= !xtmm::drift_range(q); "
              "if (__builtin_bit_cast(unsigned long long, q.u) != 0) a_min = xtmm::kDriftMin;";
@@ -256,7 +269,7 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
         c << "bad |= !" << test << ";";
         break;
       }
-      if (mode == kTest) {
+      if (mode == kTest || mode == kTestScalar) {
         c << "ok = " << test << "; ls = 0;";
         break;
       }
@@ -335,10 +348,17 @@ void read_words(std::ostringstream& s, uint32_t sig, size_t j, int32_t off) {
 // register constraint); in between, the arithmetic may move.  at(j): a
 // statement before element j, and whether the element is left out.
 template <typename At>
-void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool scalar, At at) {
+void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool scalar,
+                   bool batched, At at) {
   std::vector<int32_t> off(kd.size() + 1, 0);
   for (size_t j = 0; j < kd.size(); ++j) off[j + 1] = off[j] + n_words(kd[j]);
-  const std::vector<size_t> before = reads_ahead(kd);
+  std::vector<size_t> before = reads_ahead(kd);
+  for (size_t m = 1; scalar && m < kd.size(); ++m)
+    for (; before[m] < m; ++before[m]) {
+      int32_t held = 0;
+      for (size_t k = before[m]; k <= m; ++k) held += n_words(kd[k]);
+      if (held <= kScalarWords) break;
+    }
   if (!kd.empty()) read_words(s, kd[0], 0, 0);
   int32_t since = 0;  // parameter words since the last settled point
   for (size_t j = 0; j < kd.size(); ++j) {
@@ -350,13 +370,14 @@ void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool 
       << (settle ? ", \"+v\"(q.px), \"+v\"(q.py), \"+v\"(q.zeta)" : "") << ");\n";
     for (size_t m = j + 1; m < kd.size() && m <= j + 2; ++m)
       if (before[m] == j) read_words(s, kd[m], m, off[m]);
+    if (j > 0 && before[j] == j) read_words(s, kd[j], j, off[j]);
     const std::pair<std::string, bool> extra = at(j);
     if (!extra.first.empty()) s << "        " << extra.first << "\n";
     if (extra.second) continue;
     const std::string arr =
         n_words(kd[j]) > 0 ? "w" + std::to_string(j) : "p + " + std::to_string(off[j]);
     const std::string stmt =
-        emit(kd[j], arr, std::to_string(j), false, scalar ? kFlagScalar : kFlag);
+        emit(kd[j], arr, std::to_string(j), false, scalar ? kFlagScalar : kFlag, batched);
     if (!stmt.empty()) s << "        " << stmt << "\n";
   }
 }
@@ -407,7 +428,8 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   //   cell in registers (over 300, one wave per SIMD, 1M particles of the
   //   FODO ring 12.1 ms instead of 8.4 ms).
   // The wide form (`scalar`): the parameters come through scalar loads into
-  // scalar registers, which a fused multiply-add takes as its addend.  With
+  // scalar registers, which a fused multiply-add takes as its addend (kept
+  // negated, see xtmm::addend and wide_words).  With
   // several waves per SIMD the broadcast reads of LDS bound the rings of high
   // order multipoles (an order-10 multipole reads 11 x 16 bytes for 64 lanes
   // and computes 42 operations) and their registers kept the waves at two per
@@ -457,7 +479,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
        "// element with (a rare, divergent store); the loss record follows at the end\n"
        "// (its slot index passes through a register move, so the nine store\n"
        "// addresses are formed on this rare path instead of held in registers)\n"
-       "#define SAVE() do { int pj_; asm volatile(\"v_mov_b32 %0, %1\" : \"=v\"(pj_) : \"v\"(pi)); \\\n"
+       "#define SAVE() do { int pj_ = pi; asm volatile(\"\" : \"+v\"(pj_)); \\\n"
        "    P.x[pj_] = q.x; P.px[pj_] = q.px; P.y[pj_] = q.y; P.py[pj_] = q.py; \\\n"
        "    P.zeta[pj_] = q.zeta; P.delta[pj_] = q.delta; P.ptau[pj_] = q.ptau; \\\n"
        "    P.rpp[pj_] = q.rpp; P.rvv[pj_] = q.rvv; } while (0)\n"
@@ -653,8 +675,8 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   s <<
        "      // the cell's loss-code base lives in a VGPR so the per-element codes\n"
        "      // e0 + j are vector adds of literals, not hoisted scalar constants\n"
-       "      int e0;\n"
-       "      asm volatile(\"v_mov_b32 %0, %1\" : \"=v\"(e0) : \"s\"(enc_t + ec));\n";
+       "      int e0 = enc_t + ec;\n"
+       "      asm volatile(\"\" : \"+v\"(e0));\n";
   if (deferred)
     s << "      const int code_in = code;\n"
          "      const xtmm::Pt qc = q;\n";
@@ -666,7 +688,8 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
     s << "      " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
     const auto& kd = d.kinds[k];
     if (flagged) {
-      straight_cell(s, kd, scalar, [](size_t) { return std::make_pair(std::string(), false); });
+      straight_cell(s, kd, scalar, batched,
+                    [](size_t) { return std::make_pair(std::string(), false); });
       s << "      }\n";
       continue;
     }
@@ -738,15 +761,17 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "      if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) != 0, 0)) {\n"
          "        if (bad) {\n"
          "          q = qc;\n"
+      << (scalar ? "          const int4 rr = cells4[c];\n          const int kind = rr.x;\n" : "") <<
          "          for (int j = kind_first[kind]; j < kind_first[kind + 1]; ++j) {\n"
-      << (scalar ? "            const double* pe = prm + rc.y + elem_off[j];\n"
+      << (scalar ? "            const double* pe = prm + rr.y + elem_off[j];\n"
                  : "            const double* pe = (const double*)(p + elem_off[j]);\n")
       << "            const xtmm::Pt q0 = q;\n"
          "            bool ok = true;\n"
          "            int ls = 0;\n"
          "            switch (elem_sig[j]) {\n";
     for (size_t g = 0; g < sigs.size(); ++g) {
-      const std::string stmt = emit(sigs[g], "pe", "(j - kind_first[kind])", far_rf, kTest);
+      const std::string stmt = emit(sigs[g], "pe", "(j - kind_first[kind])", far_rf,
+                                    scalar ? kTestScalar : kTest);
       if (!stmt.empty()) s << "              case " << g << ": " << stmt << " break;\n";
     }
     s << "              default: break;\n"
@@ -922,7 +947,7 @@ std::string generate_record(const Decomp& d, bool axis) {
        "    if (act) {\n";
   for (size_t k = 0; k < d.kinds.size(); ++k) {
     s << "    " << (k ? "else if" : "if") << " (kind == " << k << ") {\n";
-    straight_cell(s, d.kinds[k], false, [&](size_t j) {
+    straight_cell(s, d.kinds[k], false, false, [&](size_t j) {
       const uint32_t kt = d.kinds[k][j] & 0xffu;
       return std::make_pair(std::string("ROW(to);"), kt == K_AP_CIRC || kt == K_AP_ELL || kt == K_AP_RECT);
     });
@@ -1040,6 +1065,16 @@ void split_table(const std::vector<uint64_t>& tab, int32_t n_el, std::vector<uin
     }
     off += 1 + nw;
   }
+}
+
+// The words of an element (n_words of them) as the wide form reads them: the
+// addends of its multiply-adds negated (xtmm::addend), which are a drift's
+// length and a multipole's coefficients below the highest order.
+void wide_words(uint32_t sig, double* w) {
+  const uint32_t kt = sig & 0xffu, order = (sig >> 8) & 0xffu;
+  if (kt == K_DRIFT) w[0] = -w[0];
+  if (kt == K_MULT || kt == K_MULT_CURV || kt == K_MULT_LR)
+    for (uint32_t m = 2; m < 2 * (order + 1); ++m) w[m] = -w[m];
 }
 
 // Whether the short sequences of the curvature term serve every bend of a
@@ -1200,16 +1235,38 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   const bool ilp = flagged || (!batched && rad_form != 3);
   // (no wide form with radiation, whose constants need the scalar registers:
   // electron ring, 131,072 particles, two turns, 13.3 ms against 11.3 ms)
-  if (flagged && rad_form == 0) k->wide_source = generate(d, style, batched, 0, true, true, axis);
-  return finish_kernel(d, generate(d, style, batched, rad_form, flagged, false, axis), "xtm_line", ilp,
-                       word_of, prm, k);
+  const bool wide = flagged && rad_form == 0;
+  if (wide) k->wide_source = generate(d, style, batched, 0, true, true, axis);
+  if (!finish_kernel(d, generate(d, style, batched, rad_form, flagged, false, axis), "xtm_line", ilp,
+                     word_of, prm, k))
+    return false;
+  if (wide) {
+    k->wide_prm = std::move(prm);
+    k->wide_sig = std::move(sig);
+    k->wide_word = std::move(word_of);
+  }
+  return true;
 }
 
 void build_wide_form(LineKernel* k) {
   if (!k->ok || k->wide_tried || k->wide_source.empty()) return;
   k->wide_tried = true;
+  std::vector<double> prm = std::move(k->wide_prm);
+  const std::vector<uint32_t> sig = std::move(k->wide_sig);
+  const std::vector<int32_t> word_of = std::move(k->wide_word);
   std::string error;
-  k->wide_fn = cached_function(k->wide_source, "xtm_line", true, &error);
+  const hipFunction_t fn = cached_function(k->wide_source, "xtm_line", true, &error);
+  if (!fn) return;
+  for (int32_t v = 0; v < k->nv; ++v)
+    for (size_t e = 0; e < sig.size(); ++e) wide_words(sig[e], &prm[v * k->stride + word_of[e]]);
+  const size_t bytes = prm.size() * sizeof(double);
+  if (hipMalloc(&k->wide_prm_d, bytes) != hipSuccess ||
+      hipMemcpy(k->wide_prm_d, prm.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
+    hipFree(k->wide_prm_d);
+    k->wide_prm_d = nullptr;
+    return;
+  }
+  k->wide_fn = fn;
 }
 
 bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKernel* k) {
@@ -1233,7 +1290,10 @@ bool build_record_kernel(const std::vector<uint64_t>& tab, int32_t n_el, LineKer
 void free_line_kernel(LineKernel* k) {
   hipFree(k->prm_d);
   hipFree(k->cells_d);
+  hipFree(k->wide_prm_d);
   k->prm_d = nullptr;
+  k->wide_prm_d = nullptr;
+  k->wide_fn = nullptr;
   k->cells_d = nullptr;
   k->ok = false;
 }
@@ -1242,20 +1302,22 @@ void free_line_kernel(LineKernel* k) {
 // per SIMD (kWideParticles) is launched on the wide form, which reads its
 // parameters with scalar loads, and on the form that stages them in LDS: the
 // alive count is on the device, and each launch ends at once unless the count
-// is its own.  `args` holds the kernel arguments, the bounds at `n_min` and
-// `n_max`.
+// is its own.  `args` holds the kernel arguments, the parameters at `prm` and
+// the bounds at `n_min` and `n_max`.
 namespace {
-hipError_t launch_forms(const LineKernel& k, int64_t grid_upper, void** args, int32_t* n_min,
-                        int32_t* n_max, hipStream_t s) {
+hipError_t launch_forms(const LineKernel& k, int64_t grid_upper, void** args, const double** prm,
+                        int32_t* n_min, int32_t* n_max, hipStream_t s) {
   const int32_t wg = line_block(k.style);
   const int64_t per_wg = (int64_t)wg * line_ppt(k.style);  // particles per workgroup
   const bool wide = k.wide_fn && grid_upper > kWideParticles;
+  *prm = k.prm_d;
   *n_min = -1;
   *n_max = wide ? kWideParticles : INT32_MAX;
   const int64_t upper = wide ? kWideParticles : grid_upper;
   hipError_t e = hipModuleLaunchKernel(k.fn, (unsigned)((upper + per_wg - 1) / per_wg), 1, 1,
                                        (unsigned)wg, 1, 1, 0, s, args, nullptr);
   if (e != hipSuccess || !wide) return e;
+  *prm = k.wide_prm_d;
   *n_min = kWideParticles;
   *n_max = INT32_MAX;
   return hipModuleLaunchKernel(k.wide_fn, (unsigned)((grid_upper + per_wg - 1) / per_wg), 1, 1,
@@ -1267,13 +1329,13 @@ hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* 
                        const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,
                        int32_t backward, KernelRef r, hipStream_t s) {
   if (grid_upper <= 0 || n_turns <= 0) return hipSuccess;
-  const double* prm = k.prm_d;
+  const double* prm = nullptr;
   const int32_t* cells = k.cells_d;
   int32_t n_cells = k.n_cells, n_min = 0, n_max = 0;
   void* args[] = {(void*)&prm, (void*)&cells, (void*)&n_cells, (void*)&n_el, (void*)&P,
                   (void*)&idx, (void*)&ctrl, (void*)&n_turns, (void*)&backward, (void*)&n_min,
                   (void*)&n_max, (void*)&r};
-  return launch_forms(k, grid_upper, args, &n_min, &n_max, s);
+  return launch_forms(k, grid_upper, args, &prm, &n_min, &n_max, s);
 }
 
 hipError_t launch_line_record(const LineKernel& k, int32_t n_el, const double* c6, int64_t n,
@@ -1295,7 +1357,7 @@ hipError_t launch_line_batched(const LineKernel& k, int32_t n_el, SoA P, const i
                                hipStream_t s) {
   if (grid_upper <= 0 || n_turns <= 0) return hipSuccess;
   if (!k.batched) return hipErrorInvalidValue;
-  const double* prm = k.prm_d;
+  const double* prm = nullptr;
   const int32_t* cells = k.cells_d;
   int32_t n_cells = k.n_cells, nv = k.nv, n_min = 0, n_max = 0;
   long long stride = (long long)k.stride;
@@ -1303,7 +1365,7 @@ hipError_t launch_line_batched(const LineKernel& k, int32_t n_el, SoA P, const i
                   (void*)&P,    (void*)&idx,   (void*)&ctrl,    (void*)&n_turns,
                   (void*)&backward, (void*)&n_min, (void*)&n_max, (void*)&r,
                   (void*)&first_slot, (void*)&nv, (void*)&stride};
-  return launch_forms(k, grid_upper, args, &n_min, &n_max, s);
+  return launch_forms(k, grid_upper, args, &prm, &n_min, &n_max, s);
 }
 
 }  // namespace xtm

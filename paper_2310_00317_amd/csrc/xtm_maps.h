@@ -26,23 +26,18 @@ __device__ __forceinline__ void refresh(Pt& q, double beta0) {
   q.bpt = beta0 * q.ptau;
 }
 
-// a b + c and c - a b.  kScalar: c is wave-uniform and sits in scalar
-// registers, where the three-operand instruction can read it; written out
-// because the compiler prefers the accumulating form, which needs c in vector
-// registers first (one move per multipole coefficient).
+// Addends in scalar registers.  The three-operand multiply-add reads one scalar
+// register pair, but the compiler prefers the accumulating instruction, whose
+// addend has to be moved into vector registers first (two moves per multipole
+// coefficient).  A negated addend has no accumulating form: so where an addend is
+// wave-uniform (kScalar) its negative n is what is kept, and a b - n has the
+// value of a b + (-n) to the last bit.  (The instruction itself is never written
+// out: between a lane read that restores a spilled scalar register and a vector
+// instruction that reads it the hardware needs two wait states, which the
+// compiler inserts for the instructions that it knows.)
 template <bool kScalar>
-__device__ __forceinline__ double fma_c(double a, double b, double c) {
-  if (!kScalar) return fma(a, b, c);
-  double d;
-  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
-  return d;
-}
-template <bool kScalar>
-__device__ __forceinline__ double fnma_c(double a, double b, double c) {
-  if (!kScalar) return fma(-a, b, c);
-  double d;
-  asm("v_fma_f64 %0, -%1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
-  return d;
+__device__ __forceinline__ double addend(double n) {
+  return kScalar ? -n : n;
 }
 
 // A value that every lane holds, kept in vector registers.
@@ -95,13 +90,12 @@ __device__ __forceinline__ double sqrt_in(double x) {
   return sqrt_in(x, h);
 }
 
-template <bool kScalar = false>
 __device__ __forceinline__ double div_by_root(double a, double root, double h) {
   double r = 2.0 * h;
   const double e = fma(-root, r, 1.0);
   r = fma(r, e, r);
   const double q = a * r;
-  const double rho = fnma_c<kScalar>(root, q, a);
+  const double rho = fma(-root, q, a);
   return fma(rho, r, q);
 }
 
@@ -217,12 +211,14 @@ __device__ __forceinline__ bool drift_range(const Pt& q) {
   return (q.opd2 > 0x1p-100) & (q.opd2 < 4.0);
 }
 
+// length: negated if kScalar (addend).
 // a_min: the smallest numerator served (kDriftMin; 0 for a particle known to
 // stay on the axis with the reference momentum, see on_axis).
 constexpr double kDriftMin = 0x1p-600;
 template <bool kScalar>
-__device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, double a_min,
+__device__ __forceinline__ void drift_flag(Pt& q, double length, int len_class, double a_min,
                                            bool& bad) {
+  const double L = addend<kScalar>(length);
   const DriftIn d = drift_in(q);
   double lp, dq;
   if (len_class == 2) {
@@ -232,7 +228,7 @@ __device__ __forceinline__ void drift_flag(Pt& q, double L, int len_class, doubl
     double h;
     const double pz = sqrt_in(d.pz2, h);
     const double b1 = 1.0 + pz;
-    lp = div_by_root<kScalar>(L, pz, h);
+    lp = div_by_root(L, pz, h);
     dq = div_in(d.a, b1);
     bad |= !(fabs(d.a) >= a_min);
     bad |= b1 == 0x1.fffffffffffffp+0;
@@ -269,15 +265,30 @@ __device__ __forceinline__ void drift_expanded(Pt& q, double L) {
 // c = (cr_N, ci_N, cr_{N-1}, ci_{N-1}, ..., cr_0, ci_0), by Horner:
 // b <- b z + c_n, re = fma(br, x, fma(-bi, y, cr)), im = fma(br, y, fma(bi, x, ci)).
 // Writes the field kick (dpx, dpy) to kx, ky.
-template <int N, bool kScalar = false>
+//   kScalar != 0: the coefficients below the highest order are negated (addend).
+// An instruction reads one scalar operand, so of the first two coefficients one
+// has to be in vector registers: 1, by a 64-bit move (a move of two words, to the
+// compiler), or 2, by an operation on doubles, whose scalar registers the
+// compiler allocates with fewer spills where they are short.  DA ring, 100,000
+// particles, 20 turns: 63.3 ms by 1, 64.3 ms by 2 (16 of them among a cell's 1,313
+// operations); a batch of 32 errored rings: 9.00 ms by 1 (45 lane moves a cell
+// from spills), 8.84 ms by 2 (10).
+template <int N, int kScalar = 0>
 __device__ __forceinline__ void multipole(Pt& q, const double* __restrict__ c, double& kx,
                                           double& ky) {
   double br = c[0], bi = c[1];
+  if (kScalar == 1 && N > 0) {
+    typedef int Words __attribute__((ext_vector_type(2)));
+    Words w = __builtin_bit_cast(Words, bi);
+    asm("" : "+v"(w));
+    bi = __builtin_bit_cast(double, w);
+  }
+  if (kScalar == 2 && N > 0) bi = __builtin_canonicalize(bi);
 #pragma unroll
   for (int k = 1; k <= N; ++k) {
-    const double cr = c[2 * k], ci = c[2 * k + 1];
-    const double tr = fma(br, q.x, fnma_c<kScalar>(bi, q.y, cr));
-    const double ti = fma(br, q.y, fma_c<kScalar>(bi, q.x, ci));
+    const double cr = addend<kScalar != 0>(c[2 * k]), ci = addend<kScalar != 0>(c[2 * k + 1]);
+    const double tr = fma(br, q.x, fma(-bi, q.y, cr));
+    const double ti = fma(br, q.y, fma(bi, q.x, ci));
     br = tr;
     bi = ti;
   }
@@ -325,55 +336,101 @@ __device__ __forceinline__ void curvature_flag(Pt& q, double hxl, double k0h, do
 //   by its odd series up to the 21st power (|s| <= 0.1716: the next term is
 //   below 2.2e-19); log x = e ln2 + log m, ln 2 split like pi/2.  Domain:
 //   finite x (sin, cos); finite x > 0 (log).
-//   The coefficients are read from scalar registers (fma_c): a literal that
-//   goes through vector registers is two moves per coefficient.
+// The series' coefficients below the leading ones, in Horner's order, negated
+// (see addend): sine (1/15! .. 1/3!) and cosine (1/14! .. 1/2!), logarithm.
+#define XTM_SINCOS_COEF                                                           \
+  {1.0 / 1307674368000.0, -1.0 / 6227020800.0, 1.0 / 39916800.0, -1.0 / 362880.0, \
+   1.0 / 5040.0, -1.0 / 120.0, 1.0 / 6.0,                                         \
+   1.0 / 87178291200.0, -1.0 / 479001600.0, 1.0 / 3628800.0, -1.0 / 40320.0,      \
+   1.0 / 720.0, -1.0 / 24.0, 1.0 / 2.0}
+#define XTM_LOG_COEF                                                          \
+  {-1.0 / 19.0, -1.0 / 17.0, -1.0 / 15.0, -1.0 / 13.0, -1.0 / 11.0, -1.0 / 9.0, \
+   -1.0 / 7.0, -1.0 / 5.0, -1.0 / 3.0}
+constexpr int kSinCosCoefs = 14, kLogCoefs = 9;
+// (not const: the compiler is not to know the values)
+static __constant__ double kSinCos[kSinCosCoefs] = XTM_SINCOS_COEF;
+
+// Where a series has its coefficients.  Literals become vector registers that
+// the compiler keeps through the whole element loop (26 of them), which suits a
+// step that every few elements take (a deviate inside a straight cell).  Code out
+// of line holds them in scalar registers, not known to the compiler.  A cavity,
+// which a few elements of a turn are, reads a table, through scalar registers or,
+// where these hold the cell's parameters (the generated kernels' wide form),
+// through vector registers.
+enum Coef { kLiteral, kHeld, kByScalar, kByVector };
+
+template <Coef kCoef>
+__device__ __forceinline__ void sincos_coef(double (&n)[kSinCosCoefs]) {
+  if (kCoef == kByScalar || kCoef == kByVector) {
+    typedef const __attribute__((address_space(4))) double* Table;
+    Table t = (Table)(unsigned long long)&kSinCos[0];
+    // (read here, not ahead of the element loop)
+    if (kCoef == kByScalar) asm volatile("" : "+s"(t));
+    else asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int k = 0; k < kSinCosCoefs; ++k) n[k] = t[k];
+    return;
+  }
+  const double c[kSinCosCoefs] = XTM_SINCOS_COEF;
+#pragma unroll
+  for (int k = 0; k < kSinCosCoefs; ++k) {
+    n[k] = c[k];
+    if (kCoef == kHeld) asm("" : "+s"(n[k]));
+  }
+}
+
+template <Coef kCoef>
+__device__ __forceinline__ void log_coef(double (&n)[kLogCoefs]) {
+  const double c[kLogCoefs] = XTM_LOG_COEF;
+#pragma unroll
+  for (int k = 0; k < kLogCoefs; ++k) {
+    n[k] = c[k];
+    if (kCoef == kHeld) asm("" : "+s"(n[k]));
+  }
+}
+
 // kTurn: |x| <= 2 pi, so the quadrant is a small integer.
-template <bool kTurn = false>
+template <Coef kCoef, bool kTurn = false>
 __device__ __forceinline__ void sincos_core(double x, double& sr, double& cr, int& quad) {
+  double c[kSinCosCoefs];
+  sincos_coef<kCoef>(c);
   const double n = rint(x * 0.6366197723675814);
   double r = fma(-n, 1.5707963267948966, x);
   r = fma(-n, 6.123233995736766e-17, r);
   r = fma(-n, -1.4973849048591698e-33, r);
   const double z = r * r;
-  double a = 1.0 / 355687428096000.0;          // 1/17!
-  a = fma_c<true>(a, z, -1.0 / 1307674368000.0);       // -1/15!
-  a = fma_c<true>(a, z, 1.0 / 6227020800.0);           // 1/13!
-  a = fma_c<true>(a, z, -1.0 / 39916800.0);            // -1/11!
-  a = fma_c<true>(a, z, 1.0 / 362880.0);               // 1/9!
-  a = fma_c<true>(a, z, -1.0 / 5040.0);                // -1/7!
-  a = fma_c<true>(a, z, 1.0 / 120.0);                  // 1/5!
-  a = fma_c<true>(a, z, -1.0 / 6.0);                   // -1/3!
+  double a = 1.0 / 355687428096000.0;  // 1/17!
+#pragma unroll
+  for (int k = 0; k < 7; ++k) a = fma(a, z, -c[k]);
   sr = fma(r * z, a, r);
-  double b = 1.0 / 20922789888000.0;           // 1/16!
-  b = fma_c<true>(b, z, -1.0 / 87178291200.0);         // -1/14!
-  b = fma_c<true>(b, z, 1.0 / 479001600.0);            // 1/12!
-  b = fma_c<true>(b, z, -1.0 / 3628800.0);             // -1/10!
-  b = fma_c<true>(b, z, 1.0 / 40320.0);                // 1/8!
-  b = fma_c<true>(b, z, -1.0 / 720.0);                 // -1/6!
-  b = fma_c<true>(b, z, 1.0 / 24.0);                   // 1/4!
-  b = fma_c<true>(b, z, -1.0 / 2.0);                   // -1/2!
+  double b = 1.0 / 20922789888000.0;  // 1/16!
+#pragma unroll
+  for (int k = 7; k < 14; ++k) b = fma(b, z, -c[k]);
   cr = fma(z, b, 1.0);
   quad = kTurn ? ((int)n & 3) : (int)((long long)n & 3);
 }
 
+template <Coef kCoef = kByScalar>
 __device__ __forceinline__ double xsin(double x) {
   double sr, cr;
   int k;
-  sincos_core(x, sr, cr, k);
+  sincos_core<kCoef>(x, sr, cr, k);
   const double v = (k & 1) ? cr : sr;
   return (k & 2) ? -v : v;
 }
 
 // cosine of x in [0, 2 pi]
+template <Coef kCoef>
 __device__ __forceinline__ double xcos_turn(double x) {
   double sr, cr;
   int k;
-  sincos_core<true>(x, sr, cr, k);
+  sincos_core<kCoef, true>(x, sr, cr, k);
   const double v = (k & 1) ? sr : cr;
   return ((k + 1) & 2) ? -v : v;
 }
 
-__device__ __forceinline__ double xlog(double x) {
+// n: log_coef
+__device__ __forceinline__ double xlog(double x, const double (&n)[kLogCoefs]) {
   int e;
   double m = frexp(x, &e);
   if (m < 0.70710678118654752440) {
@@ -387,15 +444,8 @@ __device__ __forceinline__ double xlog(double x) {
   s = b == 0x1.fffffffffffffp+0 ? -0x1.0000000000001p-53 : s;
   const double z = s * s;
   double p = 1.0 / 21.0;
-  p = fma_c<true>(p, z, 1.0 / 19.0);
-  p = fma_c<true>(p, z, 1.0 / 17.0);
-  p = fma_c<true>(p, z, 1.0 / 15.0);
-  p = fma_c<true>(p, z, 1.0 / 13.0);
-  p = fma_c<true>(p, z, 1.0 / 11.0);
-  p = fma_c<true>(p, z, 1.0 / 9.0);
-  p = fma_c<true>(p, z, 1.0 / 7.0);
-  p = fma_c<true>(p, z, 1.0 / 5.0);
-  p = fma_c<true>(p, z, 1.0 / 3.0);
+#pragma unroll
+  for (int k = 0; k < kLogCoefs; ++k) p = fma(p, z, -n[k]);
   const double t = 2.0 * s;
   const double lm = fma(t * z, p, t);
   const double de = (double)e;
@@ -414,9 +464,10 @@ __device__ __forceinline__ void from_ptau(Pt& q, double beta0, double two_over_b
 
 // Thin RF cavity: ptau += amp sin(phase - k zeta), amp = charge0 V / p0c,
 // k = 2 pi f / (beta0 c).
+template <Coef kCoef = kByScalar>
 __device__ __forceinline__ void rf(Pt& q, double amp, double k, double phase, double beta0,
                                    double two_over_beta0) {
-  const double s = xsin(phase - k * q.zeta);
+  const double s = xsin<kCoef>(phase - k * q.zeta);
   q.ptau = q.ptau + amp * s;
   from_ptau(q, beta0, two_over_beta0);
 }
@@ -426,7 +477,7 @@ __device__ __forceinline__ void rf(Pt& q, double amp, double k, double phase, do
 // the whole element loop, and cavities are rare.  (Values, not the particle,
 // go through the call: an address handed to a call keeps the particle in
 // memory through the whole kernel.)
-__device__ __attribute__((noinline)) double xsin_far(double x) { return xsin(x); }
+__device__ __attribute__((noinline)) double xsin_far(double x) { return xsin<kHeld>(x); }
 
 __device__ __forceinline__ void rf_far(Pt& q, double amp, double k, double phase, double beta0,
                                        double two_over_beta0) {
@@ -507,6 +558,7 @@ __device__ __forceinline__ double uniform52(unsigned int wa, unsigned int wb) {
 
 // Standard normal of (seed, particle id, turn, element, draw) by Box-Muller
 // on one Philox block with counter (pid_lo, pid_hi, turn, element * 8 + draw).
+template <Coef kCoef = kLiteral>
 __device__ __forceinline__ double gauss_at(unsigned long long seed, long long pid, int turn,
                                            int element, int draw) {
   U4 c;
@@ -517,12 +569,14 @@ __device__ __forceinline__ double gauss_at(unsigned long long seed, long long pi
   const U4 w = philox4x32_10(c, (unsigned int)seed, (unsigned int)(seed >> 32));
   const double u1 = uniform52(w.a, w.b), u2 = uniform52(w.c, w.d);
   // u1 in [2^-53, 1 - 2^-53]: the root's operand lies in [2^-53, 74]
-  return sqrt_in(-2.0 * xlog(u1)) * xcos_turn(6.283185307179586 * u2);
+  double n[kLogCoefs];
+  log_coef<kCoef>(n);
+  return sqrt_in(-2.0 * xlog(u1, n)) * xcos_turn<kCoef>(6.283185307179586 * u2);
 }
 
 __device__ __attribute__((noinline)) double gauss_at_far(unsigned long long seed, long long pid,
                                                          int turn, int element, int draw) {
-  return gauss_at(seed, pid, turn, element, draw);
+  return gauss_at<kHeld>(seed, pid, turn, element, draw);
 }
 
 // ------------------------------------------------------------ radiation
@@ -597,13 +651,15 @@ __device__ __attribute__((noinline)) double photon_sum(double nbar, const double
   c.a = (unsigned int)(unsigned long long)pid;
   c.b = (unsigned int)((unsigned long long)pid >> 32);
   c.c = (unsigned int)turn;
+  double n[kLogCoefs];
+  log_coef<kHeld>(n);
   double t = 0.0, sum = 0.0;
   for (int j = 0; j < 256; ++j) {
     c.d = (unsigned int)element * 256u + (unsigned int)j;
     const U4 w = philox4x32_10(c, (unsigned int)seed, (unsigned int)(seed >> 32));
-    t = t - xlog(uniform52(w.a, w.b));
+    t = t - xlog(uniform52(w.a, w.b), n);
     if (!(t <= nbar)) break;
-    sum = sum + photon_x(tab, -xlog(uniform52(w.c, w.d)));
+    sum = sum + photon_x(tab, -xlog(uniform52(w.c, w.d), n));
   }
   return sum;
 }
