@@ -232,7 +232,8 @@ typedef struct xtm_track_opts {
 typedef struct xtm_track_stats {
   int64_t passes;     /* (particle, element) applications made while alive, loss included */
   int64_t alive;      /* particles alive after the call */
-  int32_t launches;   /* tracking-kernel launches made by the call */
+  int32_t launches;   /* tracking launches made by the call (one a chunk; the two forms
+                         of variant 14, see xtm_wide_form, count as one) */
   int32_t variant;    /* tracking kernel that ran (see xtm_track_opts) */
   double kernel_ms;   /* summed duration of those launches (time_kernels = 1), else 0 */
 } xtm_track_stats;
@@ -523,6 +524,19 @@ xtm_status xtm_batch_destroy(xtm_batch b);
 xtm_status xtm_track_batched(xtm_batch b, xtm_particles p, const int64_t* first_slot,
                              int32_t n_turns, const xtm_track_opts* opts, void* stream,
                              xtm_track_stats* stats);
+
+/* The wide form of variant 14: without radiation, sets of more than 65,536
+   alive particles run on a second form of the kernel that reads the parameters
+   through scalar registers (the same results).  It is compiled by the first
+   call on such a set, besides the form for smaller sets, and its parameters are
+   a second copy on the device.  Both forms are launched for each chunk of such a
+   call, and the device's count of alive particles decides which does the chunk.
+     *state: 0 not asked for yet, 1 built, -1 could not be built: then the other
+       form serves every size, and xtm_last_error() holds the reason;
+     *launches (or NULL): its launches so far, enqueued or captured.
+   Give exactly one of `lat` and `batch` (backward = 0 with a batch). */
+xtm_status xtm_wide_form(xtm_lattice lat, xtm_batch batch, int32_t backward, int32_t* state,
+                         int64_t* launches);
 
 /* Launch-plan autotuner.  Times candidate plans on a scratch copy of the
    set (the set itself is not advanced), each for probe_turns turns through

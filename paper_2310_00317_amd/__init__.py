@@ -135,6 +135,7 @@ def lib() -> ctypes.CDLL:
             "xtm_batch_create": ([vp, i32, vp], i32),
             "xtm_batch_destroy": ([vp], i32),
             "xtm_track_batched": ([vp, vp, vp, i32, vp, vp, vp], i32),
+            "xtm_wide_form": ([vp, vp, i32, vp, vp], i32),
             "xtm_autotune": ([vp, vp, vp, vp, i32, i32, vp, vp], i32),
             "xtm_features": ([vp, i64, vp, ctypes.c_double, ctypes.c_double, vp, vp], i32),
             "xtm_feature_stats": ([vp, vp, i64, vp, vp], i32),
@@ -319,6 +320,18 @@ class Particles:
             self.close()
         except Exception:
             pass
+
+
+def wide_form(line, backward: bool = False) -> tuple:
+    """(state, launches, reason) of the wide form of variant 14 of a Lattice or Batch:
+    0 not asked for yet, 1 built, -1 could not be built (then with the reason);
+    its launches so far."""
+    state, launches = ctypes.c_int32(), ctypes.c_int64()
+    lat, batch = (None, line.handle) if isinstance(line, Batch) else (line.handle, None)
+    check(lib().xtm_wide_form(lat, batch, int(backward), ctypes.byref(state),
+                              ctypes.byref(launches)), "xtm_wide_form")
+    reason = lib().xtm_last_error().decode() if state.value < 0 else ""
+    return state.value, launches.value, reason
 
 
 def line_variants() -> list:

@@ -1048,6 +1048,21 @@ xtm_status xtm_batch_destroy(xtm_batch B) {
   return XTM_OK;
 }
 
+xtm_status xtm_wide_form(xtm_lattice lat, xtm_batch batch, int32_t backward, int32_t* state,
+                         int64_t* launches) {
+  if ((lat == nullptr) == (batch == nullptr)) return fail(XTM_E_ARG, "give a lattice or a batch");
+  if (!state) return fail(XTM_E_ARG, "null argument");
+  if (batch && backward) return fail(XTM_E_ARG, "a batch is tracked forward only");
+  int32_t style = 0;
+  while (!line_long(style)) ++style;
+  const LineKernel& k = batch ? batch->line[0][style]
+                              : (backward ? lat->bwd_line[style] : lat->fwd_line[0][style]);
+  *state = k.wide_fn ? 1 : (k.wide_tried ? -1 : 0);
+  if (*state < 0) g_err = "wide form: " + k.wide_error;
+  if (launches) *launches = k.wide_launches;
+  return XTM_OK;
+}
+
 namespace {
 xtm_status set_partition(xtm_batch_s* B, xtm_particles_s* P, const int64_t* first_slot,
                          hipStream_t s) {

@@ -188,6 +188,8 @@ struct LineKernel {
   bool wide_tried = false;
   hipFunction_t wide_fn = nullptr;
   double* wide_prm_d = nullptr;
+  std::string wide_error;             // why it could not be built
+  mutable int64_t wide_launches = 0;  // enqueued or captured
 };
 // Generated-kernel forms ("styles"), all computing the same maps in the same
 // order: the workgroup (256 lanes or one wave), the way element code reads

@@ -1254,8 +1254,7 @@ void build_wide_form(LineKernel* k) {
   std::vector<double> prm = std::move(k->wide_prm);
   const std::vector<uint32_t> sig = std::move(k->wide_sig);
   const std::vector<int32_t> word_of = std::move(k->wide_word);
-  std::string error;
-  const hipFunction_t fn = cached_function(k->wide_source, "xtm_line", true, &error);
+  const hipFunction_t fn = cached_function(k->wide_source, "xtm_line", true, &k->wide_error);
   if (!fn) return;
   for (int32_t v = 0; v < k->nv; ++v)
     for (size_t e = 0; e < sig.size(); ++e) wide_words(sig[e], &prm[v * k->stride + word_of[e]]);
@@ -1264,6 +1263,7 @@ void build_wide_form(LineKernel* k) {
       hipMemcpy(k->wide_prm_d, prm.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
     hipFree(k->wide_prm_d);
     k->wide_prm_d = nullptr;
+    k->wide_error = "device allocation for the wide form failed";
     return;
   }
   k->wide_fn = fn;
@@ -1320,6 +1320,7 @@ hipError_t launch_forms(const LineKernel& k, int64_t grid_upper, void** args, co
   *prm = k.wide_prm_d;
   *n_min = kWideParticles;
   *n_max = INT32_MAX;
+  ++k.wide_launches;
   return hipModuleLaunchKernel(k.wide_fn, (unsigned)((grid_upper + per_wg - 1) / per_wg), 1, 1,
                                (unsigned)wg, 1, 1, 0, s, args, nullptr);
 }
