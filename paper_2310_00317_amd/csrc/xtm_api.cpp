@@ -1457,7 +1457,7 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
         const int64_t start = b * batch, B = (n - start < batch) ? n - start : batch;
         e = launch_mlp_train_step(d_theta, d_m, d_v, d_norm, d_x, d_y, perm_d + start, B,
                                   pos_weight, bias + b, lr, loss + (b % 4096), work, s);
-        ++*step;
+        if (e == hipSuccess) ++*step;
       }
       // mean batch loss of the epoch (the permutation buffer is reused next epoch)
       if (e == hipSuccess) e = hipStreamSynchronize(s);

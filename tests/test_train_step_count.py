@@ -1,0 +1,37 @@
+"""The training loop's step count is that of the updates made: a step whose
+launch fails is not counted.  Run on the CPU in a process of its own, with the
+device calls answered by a library in front of them."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CALL = """
+import ctypes, sys
+import numpy as np
+L = ctypes.CDLL(sys.argv[1])
+n = 10
+a = np.zeros(20000, dtype=np.float32)
+p = a.ctypes.data_as(ctypes.c_void_p)
+step = ctypes.c_int32(7)
+code = L.xtm_mlp_train(p, p, p, p, p, p, ctypes.c_int64(n), ctypes.c_float(1.0), 2, 4,
+                       ctypes.c_float(1e-3), ctypes.c_uint64(1), ctypes.byref(step), None, None)
+print(code, step.value)
+"""
+
+
+@pytest.mark.parametrize("fail_at,steps", [(0, 0), (2, 2), (4, 4), (99, 6)])
+def test_failed_step_is_not_counted(tmp_path, fail_at, steps):
+    import paper_2310_00317_amd as P
+    stub = str(tmp_path / "stub.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    "-I/opt/rocm/include", "-w", "-o", stub,
+                    os.path.join(HERE, "cpu_emulation", "train_stub.cpp")], check=True)
+    out = subprocess.run([sys.executable, "-c", CALL, P.LIB_PATH], check=True,
+                         capture_output=True, text=True,
+                         env=dict(os.environ, LD_PRELOAD=stub, FAIL_AT=str(fail_at))).stdout
+    code, count = (int(v) for v in out.split()[-2:])
+    assert (code == 0) == (fail_at == 99)
+    assert count == 7 + steps
