@@ -114,6 +114,14 @@ __device__ void load_net(NetLds& s, const float* __restrict__ th) {
   if (threadIdx.x == 0) s.b3 = th[oB3];
 }
 
+// What lanes of a wave wrote to LDS is there for its other lanes from here on (a
+// wave's LDS operations run in order: no instruction, but the compiler is told).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ float relu(float z) { return z > 0.f ? z : 0.f; }
 
 // Features 4 q .. 4 q + 3 of row `row`; the first row's when `on` is false (a
@@ -320,7 +328,9 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const float* __restrict__ thet
     *reinterpret_cast<bf16x4*>(&s.h2[16 * w + col][16 * nt + 4 * q]) = h2t[nt];
   }
   // the logit of this lane's sample, the neurons in order (training amplifies
-  // a rounding that falls the other way, so every sum of the step has one order)
+  // a rounding that falls the other way, so every sum of the step has one order):
+  // its row comes from four lanes of this wave
+  wave_sync();
   float z = 0.f;
 #pragma unroll
   for (int k = 0; k < kH; k += 4) {
