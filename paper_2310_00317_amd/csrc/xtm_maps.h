@@ -111,11 +111,14 @@ __device__ __forceinline__ double div_in(double a, double b) {
 }
 
 // a / b with r = 1/b correctly rounded, correctly rounded itself (Markstein's
-// quotient step): near a midpoint of two quotients the product is one of the
-// two, so the step's error, half a unit times r's relative error of at most
-// b 2^-54 (b in [1, 2)), is below the distance 2^-53 / b that a quotient keeps
-// from a midpoint.  Within div_in's exponent range; three operations
-// instead of the generic division's eleven.
+// quotient step).  r is within b 2^-54 of 1/b, relatively (b in [1, 2)), so the
+// product a r, rounded, is within one and a half units of the quotient, and the
+// correction q + r (a - b q) before its rounding within |a/b - q| b 2^-54 of it.
+// That matters only next to a midpoint of two neighbours.  There the unrounded
+// product is less than a unit from the midpoint, so it is rounded to one of the
+// two, half a unit away, and the error, b 2^-55 units, is below the 2^-53 / b
+// units that a quotient keeps from a midpoint.  Within div_in's exponent range;
+// three operations instead of the generic division's eleven.
 __device__ __forceinline__ double div_known(double a, double b, double r) {
   const double q = a * r;
   return fma(fma(-b, q, a), r, q);
