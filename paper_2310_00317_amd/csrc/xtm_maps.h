@@ -711,13 +711,20 @@ __device__ __forceinline__ void radiate_at(Pt& q, double kx, double ky, double l
   radiate(q, kx, ky, lr, rr, mode, g, beta0, two_over_beta0);
 }
 
+// v with the high word `high` where `on`.
+__device__ __forceinline__ double with_high(double v, bool on, unsigned int high) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned int hi = on ? high : (unsigned int)(b >> 32);
+  return __builtin_bit_cast(double, (unsigned long long)hi << 32 | (unsigned int)b);
+}
+
 // The mean (kMode 1) or mean and Gaussian (2) radiation step without branches
 // and with the short sequences, for a cell whose tests are collected: the same
 // values as radiate(), or `bad` set.  ilr = 1/lr and ip0c = 1/p0c, correctly
 // rounded; lr and p0c in [2^-100, 2^100]; on entry q.rpp is 1/(1+delta) correctly
 // rounded and drift_range(q) holds.  What keeps the operands within the short
-// sequences' reach: the squared kick, the variance, the loss and v are tested
-// from below (from above their sequences hold to the end of the range, and an
+// sequences' reach: the squared kick (if not zero), the variance, the loss and v
+// are tested from below (from above their sequences hold to the end of the range, and an
 // infinity ends in a delta that is not a number); delta is held to (-1/2, 1/2)
 // and 1 + beta0 ptau to positive values, so that the divisors 1 + sqrt(1 + v),
 // 1 + delta and 1 + beta0 ptau lie in (1, 3), (1/2, 3/2) and (1/2, 3/2), each
@@ -733,7 +740,11 @@ template <int kMode>
 __device__ __forceinline__ void radiate_flag(Pt& q, double kx, double ky, double lr, double ilr,
                                              const Rad& rr, double ip0c, double g, double beta0,
                                              double two_over_beta0, bool& bad) {
-  const double k2 = kx * kx + ky * ky;
+  double k2 = kx * kx + ky * ky;
+  // no kick, no loss: the steps of a kick of one (k2's low word is zero) and a
+  // loss below 2^-1022, which does not reach ptau
+  const bool none = k2 == 0.0;
+  k2 = with_high(k2, none, 0x3ff00000u);
   bad |= !(k2 >= 0x1p-500);
   const double h = div_known(sqrt_in(k2) * q.rpp, lr, ilr);
   const double gam = rr.gamma0 * (1.0 + q.bpt);
@@ -747,6 +758,7 @@ __device__ __forceinline__ void radiate_flag(Pt& q, double kx, double ky, double
     de = de + sqrt_in(var) * g;
   }
   bad |= !(fabs(de) >= 0x1p-600);
+  de = with_high(de, none, 0u);
   const double opd_old = 1.0 + q.delta, rpp_old = q.rpp;
   q.ptau = q.ptau - div_known(de, rr.p0c, ip0c);
   // from_ptau

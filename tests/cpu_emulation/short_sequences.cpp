@@ -115,7 +115,9 @@ int main(int argc, char** argv) {
     q = p;
     memcpy(&g, &q, sizeof g);
   };
-  for (int mode = 1; mode <= 2; ++mode) {
+  for (int run = 0; run < 4; ++run) {
+    const int mode = 1 + run % 2;
+    const bool no_kick = run >= 2;  // (a square that underflows among them)
     long served = 0, bad = 0;
     for (long i = 0; i < n; ++i) {
       xtmm::Pt q;
@@ -124,7 +126,9 @@ int main(int argc, char** argv) {
       const double scale = rnd() % 3 ? 1e-3 : pow2(-300, 4);
       double kx = scale * sig() * sign(), ky = scale * sig() * sign();
       if (rnd() % 8 == 0) kx = 0.0;
+      if (no_kick) kx = rnd() % 8 ? 0.0 : pow2(-900, -600);
       if (rnd() % 8 == 0) ky = rnd() & 1 ? 0.0 : -0.0;
+      if (no_kick) ky = rnd() & 1 ? 0.0 : -0.0;
       const double lr = rnd() % 2 ? sig() * pow2(-3, 5) : sig() * pow2(-99, 99);
       const double p0c = sig() * pow2(30, 40), c_mean = sig() * pow2(-40, 0),
                    c_quant = sig() * pow2(-60, -20), gamma0 = sig() * pow2(8, 17);
@@ -140,7 +144,8 @@ int main(int argc, char** argv) {
       ++served;
       bad += !same_state(q, g);
     }
-    report(mode == 1 ? "radiate mean" : "radiate quantum", served, bad);
+    report(no_kick ? (mode == 1 ? "no kick, mean" : "no kick, quantum")
+                   : (mode == 1 ? "radiate mean" : "radiate quantum"), served, bad);
   }
   {
     long served = 0, bad = 0;

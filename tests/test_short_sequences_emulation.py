@@ -41,7 +41,7 @@ def test_short_sequences_give_the_general_bits(tmp_path):
     n = 2000000
     out = subprocess.run([exe, str(n)], check=True, capture_output=True, text=True).stdout
     rows = re.findall(r"^(.*) served (\d+) wrong (\d+)$", out, re.M)
-    assert len(rows) == 9, out
+    assert len(rows) == 11, out
     for what, served, wrong in rows:
         assert int(wrong) == 0, out
         assert int(served) >= n // 10, out
