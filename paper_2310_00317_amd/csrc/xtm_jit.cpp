@@ -180,9 +180,10 @@ enum EmitMode {
   kTestScalar = 7
 };
 
-// batched: for a kernel that serves a batch of lattice variants.
+// batched: for a kernel that serves a batch of lattice variants.  rf_by_vector:
+// a cavity's series reads its table through vector registers.
 std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool far_rf,
-                 EmitMode mode, bool batched = false) {
+                 EmitMode mode, bool batched = false, bool rf_by_vector = false) {
   const uint32_t kt = s & 0xffu, order = (s >> 8) & 0xffu;
   auto P = [&](int32_t m) { return "(" + arr + ")[" + std::to_string(m) + "]"; };
   const bool flag = mode == kFlag || mode == kFlagScalar;
@@ -245,7 +246,7 @@ std::string emit(uint32_t s, const std::string& arr, const std::string& j, bool 
       break;
     }
     case K_RF:
-      c << (far_rf ? "xtmm::rf_far(q, " : negated ? "xtmm::rf<xtmm::kByVector>(q, " : "xtmm::rf(q, ")
+      c << (far_rf ? "xtmm::rf_far(q, " : rf_by_vector ? "xtmm::rf<xtmm::kByVector>(q, " : "xtmm::rf(q, ")
         << P(0) << ", " << P(1) << ", " << P(2) << ", beta0, two_over_beta0);";
       if (flag)
         c << " bad |= !xtmm::drift_range(q); "
@@ -359,6 +360,13 @@ void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool 
       for (size_t k = before[m]; k <= m; ++k) held += n_words(kd[k]);
       if (held <= kScalarWords) break;
     }
+  // a cavity's table is 14 words: beside high-order multipoles it does not fit.
+  // (200 cells of a cavity, drifts and quadrupoles, 1M particles, 20 turns: 29.2
+  // ms by scalar registers, 29.9 ms by vector registers; a cavity between
+  // multipoles of order 10: 1,130 lane moves in a cell against 79.)
+  int32_t longest = 0;
+  for (uint32_t e : kd) longest = std::max(longest, n_words(e));
+  const bool rf_by_vector = scalar && longest + 14 > kScalarWords;
   if (!kd.empty()) read_words(s, kd[0], 0, 0);
   int32_t since = 0;  // parameter words since the last settled point
   for (size_t j = 0; j < kd.size(); ++j) {
@@ -377,7 +385,8 @@ void straight_cell(std::ostringstream& s, const std::vector<uint32_t>& kd, bool 
     const std::string arr =
         n_words(kd[j]) > 0 ? "w" + std::to_string(j) : "p + " + std::to_string(off[j]);
     const std::string stmt =
-        emit(kd[j], arr, std::to_string(j), false, scalar ? kFlagScalar : kFlag, batched);
+        emit(kd[j], arr, std::to_string(j), false, scalar ? kFlagScalar : kFlag, batched,
+             rf_by_vector);
     if (!stmt.empty()) s << "        " << stmt << "\n";
   }
 }
@@ -771,7 +780,7 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
          "            switch (elem_sig[j]) {\n";
     for (size_t g = 0; g < sigs.size(); ++g) {
       const std::string stmt = emit(sigs[g], "pe", "(j - kind_first[kind])", far_rf,
-                                    scalar ? kTestScalar : kTest);
+                                    scalar ? kTestScalar : kTest, batched, scalar);
       if (!stmt.empty()) s << "              case " << g << ": " << stmt << " break;\n";
     }
     s << "              default: break;\n"
