@@ -876,8 +876,10 @@ std::string generate_record(const Decomp& d, bool axis) {
        "    (to)[1] = make_double2(q.y, q.py); (to)[2] = make_double2(q.zeta, q.delta); \\\n"
        "    (to) += row; } while (0)\n"
        "// (LDS only: the rows on their way to memory are not waited for)\n"
-       "#define BARRIER() do { __builtin_amdgcn_s_waitcnt(0xc07f); \\\n"
-       "    asm volatile(\"\" ::: \"memory\"); __builtin_amdgcn_s_barrier(); \\\n"
+       "// (no access moves across it: neither a store behind the wait that is for it\n"
+       "// nor a read ahead of the barrier)\n"
+       "#define BARRIER() do { asm volatile(\"\" ::: \"memory\"); \\\n"
+       "    __builtin_amdgcn_s_waitcnt(0xc07f); __builtin_amdgcn_s_barrier(); \\\n"
        "    asm volatile(\"\" ::: \"memory\"); } while (0)\n"
        "extern \"C\" __global__ void __launch_bounds__(2 * LANES)\n"
        "// (prm without __restrict__: its loads then stay before the barriers they are\n"
