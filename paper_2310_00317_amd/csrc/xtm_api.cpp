@@ -1429,15 +1429,16 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
     const int64_t wf = mlp_workspace_floats(bmax);
     float *work = nullptr, *loss = nullptr;
     int32_t* perm_d = nullptr;
-    double2* bias = nullptr;  // an epoch's Adam corrections
+    double2* bias = nullptr;  // Adam's corrections of the next steps
     const int64_t nb = (n + batch - 1) / batch;
+    constexpr int64_t kRing = 4096;  // steps whose losses and corrections are held
     auto release = [&]() {
       hipFree(work); hipFree(loss); hipFree(perm_d); hipFree(bias);
     };
     if (hipMalloc(&work, wf * sizeof(float)) != hipSuccess ||
-        hipMalloc(&loss, 4096 * sizeof(float)) != hipSuccess ||
+        hipMalloc(&loss, kRing * sizeof(float)) != hipSuccess ||
         hipMalloc(&perm_d, n * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc(&bias, nb * sizeof(double2)) != hipSuccess) {
+        hipMalloc(&bias, std::min(nb, kRing) * sizeof(double2)) != hipSuccess) {
       release();
       return fail(XTM_E_NOMEM, "training buffers");
     }
@@ -1452,17 +1453,19 @@ xtm_status xtm_mlp_train(float* d_theta, float* d_m, float* d_v, const float* d_
         std::swap(perm[i], perm[j]);
       }
       e = hipMemcpyAsync(perm_d, perm.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, s);
-      if (e == hipSuccess) e = launch_adam_bias(bias, *step + 1, nb, s);
       for (int64_t b = 0; b < nb && e == hipSuccess; ++b) {
         const int64_t start = b * batch, B = (n - start < batch) ? n - start : batch;
-        e = launch_mlp_train_step(d_theta, d_m, d_v, d_norm, d_x, d_y, perm_d + start, B,
-                                  pos_weight, bias + b, lr, loss + (b % 4096), work, s);
+        if (b % kRing == 0)
+          e = launch_adam_bias(bias, *step + 1, std::min(nb - b, kRing), s);
+        if (e == hipSuccess)
+          e = launch_mlp_train_step(d_theta, d_m, d_v, d_norm, d_x, d_y, perm_d + start, B,
+                                    pos_weight, bias + b % kRing, lr, loss + b % kRing, work, s);
         if (e == hipSuccess) ++*step;
       }
       // mean batch loss of the epoch (the permutation buffer is reused next epoch)
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e == hipSuccess && h_epoch_loss) {
-        const int64_t k = nb < 4096 ? nb : 4096;
+        const int64_t k = std::min(nb, kRing);
         lh.resize(k);
         e = hipMemcpy(lh.data(), loss, k * sizeof(float), hipMemcpyDeviceToHost);
         double acc = 0.0;

@@ -1,6 +1,8 @@
 """The training loop's step count is that of the updates made: a step whose
-launch fails is not counted.  Run on the CPU in a process of its own, with the
-device calls answered by a library in front of them."""
+launch fails is not counted; each step has the corrections of its own number;
+and its scratch does not grow with the number of steps.  Run on the CPU in a
+process of its own, with the device calls answered by a library in front of
+them."""
 import os
 import subprocess
 import sys
@@ -12,26 +14,41 @@ CALL = """
 import ctypes, sys
 import numpy as np
 L = ctypes.CDLL(sys.argv[1])
-n = 10
+n, batch, epochs = (int(v) for v in sys.argv[3:6])
 a = np.zeros(20000, dtype=np.float32)
 p = a.ctypes.data_as(ctypes.c_void_p)
 step = ctypes.c_int32(7)
-code = L.xtm_mlp_train(p, p, p, p, p, p, ctypes.c_int64(n), ctypes.c_float(1.0), 2, 4,
+code = L.xtm_mlp_train(p, p, p, p, p, p, ctypes.c_int64(n), ctypes.c_float(1.0), epochs, batch,
                        ctypes.c_float(1e-3), ctypes.c_uint64(1), ctypes.byref(step), None, None)
-print(code, step.value)
+print(code, step.value, ctypes.c_size_t.in_dll(ctypes.CDLL(sys.argv[2]), "stub_allocated").value)
 """
 
 
-@pytest.mark.parametrize("fail_at,steps", [(0, 0), (2, 2), (4, 4), (99, 6)])
-def test_failed_step_is_not_counted(tmp_path, fail_at, steps):
+def _train(tmp_path, n, batch, epochs, fail_at):
+    """(status, steps made, bytes of scratch) of a call from step 7 on."""
     import paper_2310_00317_amd as P
     stub = str(tmp_path / "stub.so")
     subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
                     "-I/opt/rocm/include", "-w", "-o", stub,
                     os.path.join(HERE, "cpu_emulation", "train_stub.cpp")], check=True)
-    out = subprocess.run([sys.executable, "-c", CALL, P.LIB_PATH], check=True,
-                         capture_output=True, text=True,
+    out = subprocess.run([sys.executable, "-c", CALL, P.LIB_PATH, stub, str(n), str(batch),
+                          str(epochs)], check=True, capture_output=True, text=True,
                          env=dict(os.environ, LD_PRELOAD=stub, FAIL_AT=str(fail_at))).stdout
-    code, count = (int(v) for v in out.split()[-2:])
+    code, count, scratch = (int(v) for v in out.split()[-3:])
+    return code, count - 7, scratch
+
+
+@pytest.mark.parametrize("fail_at,steps", [(0, 0), (2, 2), (4, 4), (99, 6)])
+def test_failed_step_is_not_counted(tmp_path, fail_at, steps):
+    code, made, _ = _train(tmp_path, 10, 4, 2, fail_at)
     assert (code == 0) == (fail_at == 99)
-    assert count == 7 + steps
+    assert made == steps
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 100000])
+def test_scratch_of_many_steps(tmp_path, n):
+    """Batches of one row: the permutation, one row's partial gradient and a
+    fixed number of losses and corrections."""
+    code, made, scratch = _train(tmp_path, n, 1, 1, -1)
+    assert code == 0 and made == n
+    assert scratch <= 4 * n + 4 * 18818 + (4 + 16) * 4096
