@@ -529,7 +529,8 @@ xtm_status xtm_track_batched(xtm_batch b, xtm_particles p, const int64_t* first_
    alive particles run on a second form of the kernel that reads the parameters
    through scalar registers (the same results).  It is compiled by the first
    call on such a set, besides the form for smaller sets, and its parameters are
-   a second copy on the device.  Both forms are launched for each chunk of such a
+   a second copy on the device (a call whose stream is being captured does not
+   compile it).  Both forms are launched for each chunk of such a
    call, and the device's count of alive particles decides which does the chunk.
      *state: 0 not asked for yet, 1 built, -1 could not be built: then the other
        form serves every size, and xtm_last_error() holds the reason;

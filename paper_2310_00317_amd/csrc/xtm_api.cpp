@@ -576,7 +576,7 @@ xtm_status run_turns(xtm_lattice_s* L, xtm_particles_s* P, int32_t n_turns,
       }
     }
     if (lk.ok) {
-      if (P->alive_upper > kWideParticles) build_wide_form(&lk);
+      if (P->alive_upper > kWideParticles) build_wide_form(&lk, s);
       c.variant = want;
       c.line = &lk;
       c.block = line_block(want - 5);

@@ -253,8 +253,10 @@ void free_line_kernel(LineKernel* k);
 // 9.7 against 10.8 ms; FODO ring level to 131,072, then 1-4 % better; error
 // seeds 25 % better at 131,072).
 constexpr int32_t kWideParticles = 65536;
-// Compile the wide form (once; nothing if the kernel has none).
-void build_wide_form(LineKernel* k);
+// Compile the wide form (once; nothing if the kernel has none).  Not while the
+// call's stream is being captured, which a module load and an allocation would
+// end: such a call runs on the other form unless this one is there already.
+void build_wide_form(LineKernel* k, hipStream_t s);
 hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,
                        const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,
                        int32_t backward, KernelRef r, hipStream_t s);

@@ -1259,8 +1259,11 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   return true;
 }
 
-void build_wide_form(LineKernel* k) {
+void build_wide_form(LineKernel* k, hipStream_t s) {
   if (!k->ok || k->wide_tried || k->wide_source.empty()) return;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
+    return;
   k->wide_tried = true;
   std::vector<double> prm = std::move(k->wide_prm);
   const std::vector<uint32_t> sig = std::move(k->wide_sig);
