@@ -208,7 +208,14 @@ typedef struct xtm_track_opts {
                               with long cells (repeating units of up to 40
                               elements instead of 24: fewer cell boundaries per
                               turn, more code and prefetch registers).
-                              XTM_E_UNSUPPORTED if it cannot be built */
+                              XTM_E_UNSUPPORTED if it cannot be built.
+                              A per-line kernel is compiled by the first call that
+                              needs it: one for each direction and, on a line with
+                              radiating multipoles, each radiation mode, and for
+                              variant 14 one more for large sets (xtm_wide_form).  A
+                              call whose stream is being captured compiles nothing:
+                              without its kernel it runs on the interpreter, with
+                              the same results */
   int32_t radiation;       /* synchrotron radiation in multipoles with length > 0:
                               0 off, 1 mean energy loss, 2 mean + quantum excitation
                               (Gaussian, see below), 3 photon by photon (see

@@ -565,7 +565,10 @@ xtm_status run_turns(xtm_lattice_s* L, xtm_particles_s* P, int32_t n_turns,
     const int32_t form = rad_form(L->radiates, c.rad_mode);
     LineKernel& lk = B ? B->line[form][want - 5]
                        : (backward ? L->bwd_line[want - 5] : L->fwd_line[form][want - 5]);
-    if (!lk.tried && L->n_el > 0) {
+    // (not while the caller captures the stream, which a module load would end:
+    // the interpreter, with the same results, unless the kernel is there already)
+    const bool later = !lk.tried && is_capturing(s);
+    if (!lk.tried && !later && L->n_el > 0) {
       lk.tried = true;
       if (B) {
         std::vector<const std::vector<uint64_t>*> tabs;
@@ -580,7 +583,7 @@ xtm_status run_turns(xtm_lattice_s* L, xtm_particles_s* P, int32_t n_turns,
       c.variant = want;
       c.line = &lk;
       c.block = line_block(want - 5);
-    } else if (c.variant >= 5 && L->n_el > 0) {
+    } else if (c.variant >= 5 && L->n_el > 0 && !later) {
       return fail(XTM_E_UNSUPPORTED, "per-line kernel unavailable: " + lk.error);
     } else {
       c.variant = 4;

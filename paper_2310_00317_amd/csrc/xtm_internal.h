@@ -257,6 +257,7 @@ constexpr int32_t kWideParticles = 65536;
 // call's stream is being captured, which a module load and an allocation would
 // end: such a call runs on the other form unless this one is there already.
 void build_wide_form(LineKernel* k, hipStream_t s);
+bool is_capturing(hipStream_t s);
 hipError_t launch_line(const LineKernel& k, int32_t n_el, SoA P, const int32_t* idx,
                        const int32_t* ctrl, int64_t grid_upper, int32_t n_turns,
                        int32_t backward, KernelRef r, hipStream_t s);

@@ -1259,11 +1259,13 @@ bool build_line_kernel_multi(const std::vector<const std::vector<uint64_t>*>& ta
   return true;
 }
 
+bool is_capturing(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &c) == hipSuccess && c != hipStreamCaptureStatusNone;
+}
+
 void build_wide_form(LineKernel* k, hipStream_t s) {
-  if (!k->ok || k->wide_tried || k->wide_source.empty()) return;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone)
-    return;
+  if (!k->ok || k->wide_tried || k->wide_source.empty() || is_capturing(s)) return;
   k->wide_tried = true;
   std::vector<double> prm = std::move(k->wide_prm);
   const std::vector<uint32_t> sig = std::move(k->wide_sig);
