@@ -75,9 +75,9 @@ constexpr int32_t kSettleWords = 12;
 // a word, of 102): an element's words are read further ahead of it only while
 // those of the elements in between fit, else at the element itself.  Without
 // the limit the registers are spilled in the middle of a cell that has several
-// high-order multipoles in a row (three of order 10 and a drift: 201 lane moves
-// among 2,110 instructions, with it 77 among 1,984); the listed rings, two of
-// order 10 in a row among them, take the same time either way
+// high-order multipoles in a row (three of order 10 and a drift: 1,145 lane moves
+// among 3,051 instructions, with it 189 among 2,071); a batch of rings with two
+// of order 10 in a row takes the same time either way
 constexpr int32_t kScalarWords = 24;
 // cells ahead of the tracking wave that the recording kernel's other wave loads
 constexpr int32_t kAhead = 4;
@@ -438,12 +438,14 @@ std::string generate(const Decomp& d, int32_t style, bool batched, int32_t rad_f
   //   FODO ring 12.1 ms instead of 8.4 ms).
   // The wide form (`scalar`): the parameters come through scalar loads into
   // scalar registers, which a fused multiply-add takes as its addend (kept
-  // negated, see xtmm::addend and wide_words).  With
-  // several waves per SIMD the broadcast reads of LDS bound the rings of high
-  // order multipoles (an order-10 multipole reads 11 x 16 bytes for 64 lanes
-  // and computes 42 operations) and their registers kept the waves at two per
-  // SIMD; in scalar registers they cost neither (118-160 vector registers,
-  // three or four waves).  Error seeds of the FODO ring, 1M particles: 6.1e11
+  // negated, see xtmm::addend and wide_words).  With several waves per SIMD the
+  // broadcast reads of LDS bound the rings of high order multipoles (an order-10
+  // multipole reads 11 x 16 bytes for 64 lanes and computes 42 operations), and
+  // their registers kept the waves at two per SIMD.  In scalar registers they cost
+  // no LDS reads and leave three or four waves (93-122 vector registers on the
+  // FODO, DA and errored rings); what they cost is scalar registers, of which the
+  // loop's own are spilled (44-90 of them; in the hot cell 41 lane moves of 1,487
+  // instructions on the errored ring, none on the other two).  Error seeds of the FODO ring, 1M particles: 6.1e11
   // -> 8.8e11 passes/s; DA ring, 131,072: 6.3e11 -> 7.8e11; FODO ring, 1M:
   // 1.95e12 -> 2.0e12.  A lone wave waits longer for scalar loads (one every
   // 64 bytes) than for LDS: DA ring, 40,000 particles, 3.8e11 against 4.05e11.

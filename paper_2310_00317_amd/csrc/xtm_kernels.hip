@@ -948,9 +948,9 @@ hipError_t launch_record(const uint64_t* fwd, const int32_t* seg, int32_t n_seg,
 // separate products and sums elsewhere).
 //   What bounds it: issue slots, about 100 instructions per pass (60,000
 // particles, 54 % lost, 64 vertices, ds = 0.01 m, 160 million tests: 5.07 ms ->
-// 0.71 ms; every lane against every edge, the vertices from LDS, took 16
+// 0.67 ms; every lane against every edge, the vertices from LDS, took 16
 // clocks of the CU's LDS per edge), and with few sub-steps the elements between
-// the apertures (0.1 m: 0.66 ms -> 0.21 ms; 30 dependent bisections one by one
+// the apertures (0.1 m: 0.66 ms -> 0.20 ms; 30 dependent bisections one by one
 // were 0.08 ms of that).
 namespace xtm {
 namespace {

@@ -824,8 +824,8 @@ __global__ void __launch_bounds__(T, 4) k_features(const float* __restrict__ rec
 // t / 4, t / 4 + 256, ... (a wave reads 16 rows, 1 KB, at once, eight rows of a
 // thread in flight), then the sums are reduced pairwise; norm = [mean[16],
 // inv_std[16]].  What bounds it: one CU's reads (a second workgroup would
-// need memory for its sums, which this call is not given): 0.63 ms for 2^20
-// rows, 107 GB/s; 2.06 ms when a thread read whole rows one after the other.
+// need memory for its sums, which this call is not given): 0.64 ms for 2^20
+// rows, 105 GB/s; 2.06 ms when a thread read whole rows one after the other.
 __global__ void __launch_bounds__(1024) k_feature_stats(const float* __restrict__ f,
                                                         const int32_t* __restrict__ mask,
                                                         int64_t n, float* __restrict__ norm) {

@@ -358,8 +358,9 @@ static __constant__ double kSinCos[kSinCosCoefs] = XTM_SINCOS_COEF;
 // step that every few elements take (a deviate inside a straight cell).  Code out
 // of line holds them in scalar registers, not known to the compiler.  A cavity,
 // which a few elements of a turn are, reads a table, through scalar registers or,
-// where these hold the cell's parameters (the generated kernels' wide form),
-// through vector registers.
+// beside high-order multipoles in the generated kernels' wide form, through
+// vector registers.  Cavity's literals: DA ring 149 vector registers instead of
+// 115, three waves per SIMD instead of four.
 enum Coef { kLiteral, kHeld, kByScalar, kByVector };
 
 template <Coef kCoef>
@@ -646,7 +647,8 @@ __device__ __forceinline__ double photon_x(const double* __restrict__ tab, doubl
 // (out of line: its loop would hold registers across the whole element loop).
 // Two turns of the electron ring with 100,003 particles: 46.4 ms when the call
 // took the particle's address and each Philox product and uniform the generic
-// operations, 33.8 ms now.
+// operations, 33.4 ms now (the logarithm's coefficients are set once, ahead of the
+// loop: set at each use, 10 % more for 1,000 particles).
 __device__ __attribute__((noinline)) double photon_sum(double nbar, const double* __restrict__ tab,
                                                        unsigned long long seed, long long pid,
                                                        int turn, int element) {
@@ -732,10 +734,11 @@ __device__ __forceinline__ double with_high(double v, bool on, unsigned int high
 //   What bounds it: issue slots.  On the electron ring a bend took some 440
 // vector instructions, seven generic divisions, four generic roots and a
 // deviate by call among them; it takes about 290 with these sequences, the
-// deviate inline (its scalar coefficients, one 64-bit product per Philox
-// multiplication): 100,003 particles, 4 turns, 35.9 ms -> 21.1 ms with quantum
-// excitation; 1,000 particles, 2 turns, 10.7 ms -> 6.3 ms (the mean loss alone
-// 6.3 ms -> 3.7 ms).
+// deviate inline (its coefficients literals, one 64-bit product per Philox
+// multiplication): 100,003 particles, 4 turns, 35.9 ms -> 20.8 ms with quantum
+// excitation; 1,000 particles, 2 turns, 10.7 ms -> 6.2 ms (the mean loss alone
+// 6.3 ms -> 3.7 ms).  The zero kick's selects are 0.15 ms of the 20.8; without
+// them a ring with correctors at zero took every cell twice.
 template <int kMode>
 __device__ __forceinline__ void radiate_flag(Pt& q, double kx, double ky, double lr, double ilr,
                                              const Rad& rr, double ip0c, double g, double beta0,
