@@ -48,10 +48,10 @@ TRAFFIC_SOURCES = ("xtm_jit.cpp", "xtm_maps.h")
 MEASURED_TRAFFIC = {
     # (workload, particles, turns per step, kernel variant, source hash):
     #     (bytes per launch, profile)
-    ("cfg2", 100000, 1000, 14, "82a15791a373ae66"):
-        (21813952.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
-    ("cfg1sat", 1048576, 1000, 14, "82a15791a373ae66"):
-        (189331730.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
+    ("cfg2", 100000, 1000, 14, "4b935c4c3904ef7f"):
+        (21814170.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
+    ("cfg1sat", 1048576, 1000, 14, "4b935c4c3904ef7f"):
+        (189320807.0, "profiles/xtm_line_cfg2_hbm_counters.txt"),
 }
 
 
